@@ -129,7 +129,6 @@ int ensure_device(DevPlan* d) {
     std::vector<char> buf(t.total, 0);
     put(buf, t.passes, P.passes);
     put(buf, t.stages, P.stages);
-    put(buf, t.flips, P.flips);
     put(buf, t.phases, P.phases);
     put(buf, t.twid, P.twid);
     put(buf, t.urefs, P.urefs);
@@ -184,7 +183,6 @@ PassLaunch base_launch(DevPlan* d, void* ws, int op) {
     PassLaunch L{};
     L.passes = at<Pass>(P.d_tables, t.passes);
     L.stages = at<Stage>(P.d_tables, t.stages);
-    L.flips = at<Flip>(P.d_tables, t.flips);
     L.phases = at<PhaseOp>(P.d_tables, t.phases);
     L.twid = at<double>(P.d_tables, t.twid);
     L.urefs = at<URef>(P.d_tables, t.urefs);

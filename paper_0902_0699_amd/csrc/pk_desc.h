@@ -98,9 +98,33 @@ enum StepBits : int32_t {
     ST_MAT4B = 16384,
 };
 
-// 16-byte aligned so that the slot table (phase_pm .. phase_tt) can be read as
-// four aligned 16-byte words.
-struct alignas(16) Stage {
+// The words of a stage that the tile loop reads sit in `head`, its first 96 bytes: the
+// first eight, which every stage needs, in one scalar load, each later group in one
+// load where its step is present.  A pass of one tile a workgroup is a chain of
+// latencies: with each field read where it was used, a workgroup took ~50 dependent
+// scalar round trips and one scalar-cache miss per descriptor line (26 at n_q = 12),
+// one after the other.
+enum HeadWord {
+    HD_STEPS = 0,      // StepBits
+    HD_RB = 1,         // rb[a] in 4 bits each (15: unused), nlanes from bit 24
+    HD_RBS = 2,        // rbs[q] in 4 bits each, unused entries 15 (inserting a zero bit there
+                       // leaves any thread index unchanged)
+    HD_LANES = 3,
+    HD_LANES_REST = 4,
+    HD_BITS = 5,       // hmask1, hmask2 << 5, mat_pre_a << 10, mat_post_a << 13, d2b_a << 16
+    HD_MAT_PRE = 6, HD_MAT_POST = 7,
+    HD_FLIP_PRE = 8,   // tile, local label of the flipped amplitude
+    HD_FLIP_MID = 10,
+    HD_READ = 12,      // tile, local label, readout slot
+    HD_MAT4 = 15, HD_MAT4B = 16,
+    HD_SEED = 20,      // tile, local label, instance
+    HD_WORDS = 24,
+};
+
+// 64-byte aligned: the head fills whole scalar-cache lines from the first on, and the
+// slot table (phase_pm .. phase_tt) can be read as four aligned 16-byte words.
+struct alignas(64) Stage {
+    int32_t head[HD_WORDS];
     int32_t steps;            // StepBits of the steps below that are present
     int32_t rb[kMaxRegBits];  // local tile bit held by register bit a (-1 when unused)
     int32_t rbs[kMaxRegBits]; // the same bits sorted ascending (-1 entries last)
@@ -155,14 +179,6 @@ static_assert(offsetof(Stage, phase_pm) % 16 == 0 && offsetof(Stage, phase_cnt) 
                   offsetof(Stage, phase_ut0) % 16 == 0 && offsetof(Stage, phase_ut1) == offsetof(Stage, phase_ut0) + 16 &&
                   offsetof(Stage, phase_ttm) == offsetof(Stage, phase_ut0) + 32,
               "slot table must be four consecutive aligned 16-byte words");
-static_assert(offsetof(Stage, mat_pre_a) % 16 == 0 && offsetof(Stage, mat_pre) == offsetof(Stage, mat_pre_a) + 4 &&
-                  offsetof(Stage, hmask1) == offsetof(Stage, mat_pre_a) + 8 &&
-                  offsetof(Stage, flip_mid) == offsetof(Stage, mat_pre_a) + 12 &&
-                  offsetof(Stage, hmask2) == offsetof(Stage, mat_pre_a) + 16 &&
-                  offsetof(Stage, mat_post_a) == offsetof(Stage, mat_pre_a) + 20 &&
-                  offsetof(Stage, mat_post) == offsetof(Stage, mat_pre_a) + 24,
-              "one-qubit step parameters must be two consecutive aligned 16-byte words");
-
 // One amplitude addressed by (tile, local label) in a given pass.
 struct Flip {
     int64_t tile;
@@ -193,11 +209,6 @@ constexpr int64_t kStreamBytes = (int64_t)1 << 30;
 
 constexpr int kMaxRuns = 16;
 
-// A run (src, len, dst) moves bits src..src+len-1 of a label to dst..dst+len-1.
-struct Run {
-    int32_t src, len, dst, pad;
-};
-
 // A tile-part product table of a pass: its first Plan::twid entry and the
 // tile-index bits that index it.
 struct URef {
@@ -206,33 +217,38 @@ struct URef {
     int64_t mask;
 };
 
-struct Pass {
+// Thread-index bits of the largest workgroup (1024 threads).
+constexpr int kMaxThreadBits = 10;
+
+// The offsets a thread and its registers read and write a tile at are sums over
+// index bits, so the plan holds one element offset per thread bit and per register
+// bit of the first stage (read) and of the last stage (write, which differs after
+// SWAPs done by relabelling), and the runs of the tile index as (mask, shift): all
+// that a workgroup needs before its first load, in the first lines of the record.
+struct alignas(64) Pass {
     int32_t k;           // tile bits
     int32_t nstages;
     int32_t stage_begin;
     int32_t flags;
     int64_t ntiles;      // 2^(nq - k)
     int64_t state_off;   // element offset of the instance in the packed buffer
-    double scale;        // applied by OP_SCALE
-    int32_t part_base;   // norm partials: part_base + tile
-    int32_t kmax;        // kernel instance (workgroup = 2^(kmax - rbits) threads)
-    int32_t rbits;       // register bits per thread
-    int32_t ntrun;       // runs of consecutive tile bits
-    int32_t nfrun;       // runs of consecutive free bits
-    int32_t nstrun;      // runs of the store map
-    int32_t uref_begin;  // first URef of the pass
-    int32_t nuref;       // number of them (at most kMaxURefs)
     int32_t walk;        // tiles of workgroup w in a single-instance launch over a grid of G:
                          // 0: w, w + G, ...; c > 1: runs of c consecutive tiles starting at
                          // w c, (w + G) c, ...; -1: one contiguous block of ceil(ntiles / G)
     int32_t overlap;     // single-instance launch, forward pass of full tiles: 1 keeps the next
                          // tile's loads in flight through the LDS exchanges (see run_tiles)
-    int32_t tpos[16];    // global bit position of local tile bit l when the tile is read
-    int32_t stpos[16];   // ... when it is written (differs after SWAPs done by relabelling)
-    Run trun[kMaxRuns];  // local tile label -> state label (read)
-    Run strun[kMaxRuns]; // local tile label -> state label (write)
-    Run frun[kMaxRuns];  // tile index -> state label
+    int32_t uref_begin;  // first URef of the pass
+    int32_t nuref;       // number of them (at most kMaxURefs)
+    int32_t part_base;   // norm partials: part_base + tile
+    int32_t nfrun;       // runs of consecutive free bits
+    double scale;        // applied by OP_SCALE
+    uint32_t fmask[kMaxRuns];   // tile index -> state label: OR of (t & fmask[q]) << fshift[q]
+    uint32_t fshift[kMaxRuns];
+    uint32_t lthr[kMaxThreadBits], lreg[kMaxRegBits], pad0;  // read: element offset per thread / register bit
+    uint32_t sthr[kMaxThreadBits], sreg[kMaxRegBits], pad1;  // write
 };
+static_assert(offsetof(Pass, fmask) == 64 && offsetof(Pass, lthr) % 64 == 0 && offsetof(Pass, sthr) % 64 == 0,
+              "the groups of a pass record start on scalar-cache lines");
 
 // Per-instance entry of a batched launch: one workgroup runs all passes of
 // one instance, so no two workgroups ever depend on each other.

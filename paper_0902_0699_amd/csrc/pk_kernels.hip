@@ -139,7 +139,6 @@ static KArgs kargs(const PassLaunch& L) {
     KArgs a;
     a.passes = L.passes;
     a.stages = L.stages;
-    a.flips = L.flips;
     a.phases = L.phases;
     a.twid = L.twid;
     a.urefs = L.urefs;

@@ -10,7 +10,6 @@ namespace pk {
 struct PassLaunch {
     const Pass* passes;
     const Stage* stages;
-    const Flip* flips;
     const PhaseOp* phases;
     const double* twid;  // product tables of the controlled phases (re, im pairs)
     const URef* urefs;   // tile-part tables of each pass

@@ -54,34 +54,46 @@ __device__ __forceinline__ unsigned phys(unsigned j) {
     return j ^ (((j >> W) ^ (j >> (2 * W)) ^ (j >> (3 * W))) & M);
 }
 
+typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+typedef int32_t i32x8 __attribute__((ext_vector_type(8)));
+
+// The first words of a stage's head (up to HD_MAT_POST), in one scalar load.  What
+// bounds a pass of few tiles is the latency of such reads: grouped like this, and with
+// the offsets of Pass, the passes of the n_q = 20 search went from 24.0 to 21.0 us
+// each, an FP32 iteration at n_q = 25 from 632 to 563 us, 26 two-qubit gates at
+// n_q = 27 from 5.38 to 5.22 ms.
+__device__ __forceinline__ i32x8 load_head(const PK_CONST Stage* S) {
+    return *reinterpret_cast<const PK_CONST i32x8*>(S->head);
+}
+
 // Layout of one stage: per-thread label base and the uniform offsets of the
-// four register bits (as labels and as LDS slots).
+// register bits, as labels and as byte offsets of the swizzled LDS slots.
 struct Layout {
     unsigned jt;               // thread's label base
-    unsigned pj;               // phys(jt)
-    unsigned r[kMaxRegBits];   // 1 << rb[a] (0 for missing bits)
-    unsigned p[kMaxRegBits];   // phys(1 << rb[a])
+    unsigned pj;               // phys(jt) in bytes
+    unsigned rb;               // rb[a] in 4 bits each (15: unused): the registers' offsets
+                               // follow from it where they are needed
 };
 
 template <int ESZ>
-__device__ __forceinline__ Layout make_layout(const PK_CONST Stage* S, int nrb, unsigned tid) {
+__device__ __forceinline__ Layout make_layout(const i32x8& h, unsigned tid) {
     Layout L;
+    const unsigned rb = (unsigned)h[HD_RB], rbs = (unsigned)h[HD_RBS];
     unsigned t = tid;
-    if (S->nlanes == 0) {
-        // spread the thread index over the local bits that are not register bits
-        for (int q = 0; q < nrb; ++q) {
-            const int p = S->rbs[q];
-            t = ((t >> p) << (p + 1)) | (t & ((1u << p) - 1u));
-        }
+    if ((rb >> 24) == 0u) {
+        // spread the thread index over the local bits that are not register bits: a zero
+        // inserted at bit p doubles the part of t from bit p up
+#pragma unroll
+        for (int q = 0; q < kMaxRegBits; ++q) t += t & (~0u << ((rbs >> (4 * q)) & 15u));
     } else {
         // the low W thread bits to the chosen local bits, one per swizzle group bit,
         // the others in order to the remaining free bits (the masks are uniform)
         constexpr int W = ESZ == 16 ? 4 : 5;
-        const unsigned lanes = S->lanes;
+        const unsigned lanes = (unsigned)h[HD_LANES];
         t = 0u;
 #pragma unroll
         for (int i = 0; i < W; ++i) t |= ((tid >> i) & 1u) << ((lanes >> (4 * i)) & 15u);
-        unsigned rest = S->lanes_rest, x = tid >> W;
+        unsigned rest = (unsigned)h[HD_LANES_REST], x = tid >> W;
         while (rest != 0u) {
             const unsigned low = rest & (0u - rest);
             if (x & 1u) t |= low;
@@ -90,56 +102,59 @@ __device__ __forceinline__ Layout make_layout(const PK_CONST Stage* S, int nrb, 
         }
     }
     L.jt = t;
-    L.pj = phys<ESZ>(t);
-#pragma unroll
-    for (int a = 0; a < kMaxRegBits; ++a) {
-        L.r[a] = a < nrb ? (1u << S->rb[a]) : 0u;
-        L.p[a] = phys<ESZ>(L.r[a]);
-    }
+    L.pj = phys<ESZ>(t) * ESZ;
+    L.rb = rb;
     return L;
 }
 
-__device__ __forceinline__ unsigned roff(const Layout& L, int i) {
-    return ((i & 1) ? L.r[0] : 0u) | ((i & 2) ? L.r[1] : 0u) | ((i & 4) ? L.r[2] : 0u) |
-           ((i & 8) ? L.r[3] : 0u) | ((i & 16) ? L.r[4] : 0u);
-}
-__device__ __forceinline__ unsigned poff(const Layout& L, int i) {
-    return ((i & 1) ? L.p[0] : 0u) ^ ((i & 2) ? L.p[1] : 0u) ^ ((i & 4) ? L.p[2] : 0u) ^
-           ((i & 8) ? L.p[3] : 0u) ^ ((i & 16) ? L.p[4] : 0u);
-}
-
-// Moves the bits of `x` along the runs (src, len, dst).
-__device__ __forceinline__ int64_t deposit(int64_t x, const PK_CONST Run* run, int nrun) {
-    int64_t r = 0;
-    for (int q = 0; q < nrun; ++q) {
-        const int src = run[q].src, len = run[q].len, dst = run[q].dst;
-        r |= ((x >> src) & (((int64_t)1 << len) - 1)) << dst;
+// The label of register bit a (0 for a missing bit) and the labels of the registers;
+// their LDS byte offsets are the swizzled labels.
+struct RegBits {
+    unsigned r[kMaxRegBits];
+    __device__ __forceinline__ unsigned operator()(int i) const {
+        return ((i & 1) ? r[0] : 0u) ^ ((i & 2) ? r[1] : 0u) ^ ((i & 4) ? r[2] : 0u) ^ ((i & 8) ? r[3] : 0u) ^
+               ((i & 16) ? r[4] : 0u);
     }
-    return r;
+};
+
+__device__ __forceinline__ RegBits reg_labels(const Layout& L) {
+    RegBits b;
+#pragma unroll
+    for (int a = 0; a < kMaxRegBits; ++a) b.r[a] = (1u << ((L.rb >> (4 * a)) & 15u)) & 0x7fffu;
+    return b;
 }
 
-// State offsets of a stage used for HBM access: the thread's part (elements)
-// and the uniform parts of the four register bits.
+template <int ESZ>
+__device__ __forceinline__ RegBits reg_slots(const Layout& L) {
+    RegBits b = reg_labels(L);
+#pragma unroll
+    for (int a = 0; a < kMaxRegBits; ++a) b.r[a] = phys<ESZ>(b.r[a]) * ESZ;
+    return b;
+}
+
+// State offsets (elements) of a stage used for HBM access: the thread's part and
+// the uniform parts of the register bits.  They are OR-sums of the plan's per-bit
+// offsets; `TB` is the number of thread-index bits.
 struct GOff {
-    int64_t gt;
+    uint32_t gt;
     int64_t g[kMaxRegBits];
 };
 
-// `store` selects the map the tile is written with (SWAPs done by relabelling
-// make it differ from the map it is read with).
-__device__ __forceinline__ GOff make_goff(const PK_CONST Pass* P, const PK_CONST Stage* S, const Layout& L,
-                                          int nrb, bool store) {
+template <int TB>
+__device__ __forceinline__ GOff make_goff(const PK_CONST uint32_t* thr, const PK_CONST uint32_t* reg, unsigned tid) {
     GOff G;
-    G.gt = store ? deposit((int64_t)L.jt, P->strun, P->nstrun) : deposit((int64_t)L.jt, P->trun, P->ntrun);
-    const PK_CONST int32_t* pos = store ? P->stpos : P->tpos;
+    uint32_t g = 0u;
 #pragma unroll
-    for (int a = 0; a < kMaxRegBits; ++a) G.g[a] = a < nrb ? ((int64_t)1 << pos[S->rb[a]]) : 0;
+    for (int i = 0; i < TB; ++i) g |= (0u - ((tid >> i) & 1u)) & thr[i];
+    G.gt = g;
+#pragma unroll
+    for (int a = 0; a < kMaxRegBits; ++a) G.g[a] = reg[a];
     return G;
 }
 
 __device__ __forceinline__ int64_t goff(const GOff& G, int i) {
-    return ((i & 1) ? G.g[0] : 0) + ((i & 2) ? G.g[1] : 0) + ((i & 4) ? G.g[2] : 0) +
-           ((i & 8) ? G.g[3] : 0) + ((i & 16) ? G.g[4] : 0);
+    return ((i & 1) ? G.g[0] : 0) + ((i & 2) ? G.g[1] : 0) + ((i & 4) ? G.g[2] : 0) + ((i & 8) ? G.g[3] : 0) +
+           ((i & 16) ? G.g[4] : 0);
 }
 
 // ---------------------------------------------------------------------------- gate bodies
@@ -392,7 +407,6 @@ __device__ __forceinline__ void apply_phases(const KArgs& a, const PK_CONST Stag
     const PK_CONST PhaseOp* ph = cptr(a.phases) + S->phase_first;
     // the sub-stage's slot table in 16-byte loads issued together (reading the
     // fields where they are used costs one scalar round trip per field and slot)
-    typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
     const i32x4 pms = *reinterpret_cast<const PK_CONST i32x4*>(S->phase_pm);
     const i32x4 cnts = *reinterpret_cast<const PK_CONST i32x4*>(S->phase_cnt);
     const i32x4 ucnts = *reinterpret_cast<const PK_CONST i32x4*>(S->phase_ucnt);
@@ -496,12 +510,12 @@ __device__ __forceinline__ void apply_d2bwd(T (&v)[NV][NR], int a, const R (&mh)
 struct PassCtx {
     int nrb, nreg, flags, nstages;
     bool active;
-    Layout L0, Ll;  // first (load) and last (store) stage layouts
-    GOff G0, Gl;
+    GOff G0, Gl;  // where the first stage reads and the last stage writes
 };
 
-template <int ESZ, int RB>
-__device__ __forceinline__ PassCtx make_ctx(const KArgs& a, const PK_CONST Pass* P) {
+// What the first tile's loads need: read from the pass record alone.
+template <int KMAX, int RB>
+__device__ __forceinline__ PassCtx make_ctx(const PK_CONST Pass* P) {
     PassCtx C;
     const int k = P->k;
     C.nrb = k < RB ? k : RB;
@@ -510,13 +524,34 @@ __device__ __forceinline__ PassCtx make_ctx(const KArgs& a, const PK_CONST Pass*
     C.nstages = P->nstages;
     const unsigned nact = k >= RB ? (1u << (k - RB)) : 1u;
     C.active = threadIdx.x < nact;
-    const PK_CONST Stage* S0 = cptr(a.stages) + P->stage_begin;
-    const PK_CONST Stage* Sl = S0 + (C.nstages - 1);
-    C.L0 = make_layout<ESZ>(S0, C.nrb, threadIdx.x);
-    C.Ll = make_layout<ESZ>(Sl, C.nrb, threadIdx.x);
-    C.G0 = make_goff(P, S0, C.L0, C.nrb, false);
-    C.Gl = make_goff(P, Sl, C.Ll, C.nrb, true);
+    C.G0 = make_goff<KMAX - RB>(P->lthr, P->lreg, threadIdx.x);
+    C.Gl = make_goff<KMAX - RB>(P->sthr, P->sreg, threadIdx.x);
     return C;
+}
+
+// Reads a line of each of the pass's first stages, all at the same time, so that the
+// tile loop finds their heads in the scalar cache (one after the other, each first
+// read would wait for memory).
+__device__ __forceinline__ void warm_stages(const KArgs& a, const PK_CONST Pass* P, int nstages) {
+    const PK_CONST Stage* S = cptr(a.stages) + P->stage_begin;
+    int32_t w = 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const PK_CONST Stage* Si = S + (i < nstages ? i : nstages - 1);
+        w ^= Si->head[HD_STEPS] ^ Si->head[HD_MAT4B];
+    }
+    __asm__ volatile("" ::"s"(w));
+}
+
+// A copy of the register offsets that the compiler takes as new: their sums over
+// register bits are then added up for each tile (two scalar instructions a load)
+// instead of hoisted out of the tile loop, where up to 64 of them held scalar
+// registers and were spilled to vector lanes.
+__device__ __forceinline__ GOff opaque(const GOff& g) {
+    GOff o = g;
+#pragma unroll
+    for (int a = 0; a < kMaxRegBits; ++a) __asm__ volatile("" : "+s"(o.g[a]));
+    return o;
 }
 
 // Nontemporal (streaming) 16- or 8-byte accesses of one complex amplitude.
@@ -560,12 +595,13 @@ __device__ __forceinline__ void load_tile(const KArgs& a, const PassCtx& C, int6
     const char* in0 = reinterpret_cast<const char*>((C.flags & PASS_FIRST) ? a.src0 : a.dst0);
     const char* in1 = reinterpret_cast<const char*>(a.dst1);
     const bool read1 = NV == 2 && !(C.flags & PASS_SEED_V1);
+    const GOff G0 = opaque(C.G0);
     if (!(C.flags & PASS_WIDE)) {
-        const uint32_t lane = (uint32_t)C.G0.gt * (uint32_t)sizeof(T);
+        const uint32_t lane = G0.gt * (uint32_t)sizeof(T);
 #pragma unroll
         for (int i = 0; i < NR; ++i) {
             if (i >= C.nreg) continue;
-            const int64_t u = (base + goff(C.G0, i)) * (int64_t)sizeof(T);
+            const int64_t u = (base + goff(G0, i)) * (int64_t)sizeof(T);
             if constexpr (NT)
                 v[0][i] = load_stream(reinterpret_cast<const T*>(in0 + u + lane));
             else
@@ -577,7 +613,7 @@ __device__ __forceinline__ void load_tile(const KArgs& a, const PassCtx& C, int6
 #pragma unroll
         for (int i = 0; i < NR; ++i) {
             if (i >= C.nreg) continue;
-            const int64_t e = base + C.G0.gt + goff(C.G0, i);
+            const int64_t e = base + (int64_t)G0.gt + goff(G0, i);
             v[0][i] = reinterpret_cast<const T*>(in0)[e];
             if constexpr (NV == 2)
                 if (read1) v[1][i] = reinterpret_cast<const T*>(in1)[e];
@@ -594,12 +630,13 @@ __device__ __forceinline__ void store_tile(const KArgs& a, const PassCtx& C, int
     char* out0 = reinterpret_cast<char*>(a.dst0);
     char* out1 = reinterpret_cast<char*>(a.dst1);
     const bool write0 = !(C.flags & PASS_SKIP_V0);
+    const GOff Gl = opaque(C.Gl);
     if (!(C.flags & PASS_WIDE)) {
-        const uint32_t lane = (uint32_t)C.Gl.gt * (uint32_t)sizeof(T);
+        const uint32_t lane = Gl.gt * (uint32_t)sizeof(T);
 #pragma unroll
         for (int i = 0; i < NR; ++i) {
             if (i >= C.nreg) continue;
-            const int64_t u = (base + goff(C.Gl, i)) * (int64_t)sizeof(T);
+            const int64_t u = (base + goff(Gl, i)) * (int64_t)sizeof(T);
             if constexpr (NT) {
                 if (write0) store_stream(reinterpret_cast<T*>(out0 + u + lane), v[0][i]);
             } else {
@@ -611,32 +648,32 @@ __device__ __forceinline__ void store_tile(const KArgs& a, const PassCtx& C, int
 #pragma unroll
         for (int i = 0; i < NR; ++i) {
             if (i >= C.nreg) continue;
-            const int64_t e = base + C.Gl.gt + goff(C.Gl, i);
+            const int64_t e = base + (int64_t)Gl.gt + goff(Gl, i);
             if (write0) reinterpret_cast<T*>(out0)[e] = v[0][i];
             if constexpr (NV == 2) reinterpret_cast<T*>(out1)[e] = v[1][i];
         }
     }
 }
 
-// One-amplitude steps on the element flips[f] when it lies in this tile and
-// thread: KIND 0 negates it (Oracle, Inv's C_0), 1 stores |C|^2 to its readout
+// One-amplitude steps on the element el (tile, local label, slot) when it lies in this
+// tile and thread: KIND 0 negates it (Oracle, Inv's C_0), 1 stores |C|^2 to its readout
 // slot, 2 seeds lambda = dL * psi there.  Written as selects, so the register
 // tile is updated in place.
 template <int NV, int NR, int KIND, typename T>
-__device__ __forceinline__ void element_op(const KArgs& a, T (&v)[NV][NR], const Layout& L, int f, int64_t tile,
-                                           int nreg, bool active) {
-    const PK_CONST Flip* fl = cptr(a.flips) + f;
-    if (fl->tile != tile || !active) return;
-    const unsigned jrel = (unsigned)fl->j ^ L.jt;
+__device__ __forceinline__ void element_op(const KArgs& a, T (&v)[NV][NR], const Layout& L,
+                                           const PK_CONST int32_t* el, int64_t tile, int nreg, bool active) {
+    if (el[0] != (int)tile || !active) return;
+    const unsigned jrel = (unsigned)el[1] ^ L.jt;
+    const int slot = KIND == 0 ? 0 : el[2];
+    const RegBits roff = reg_labels(L);
     unsigned rmask = 0;
 #pragma unroll
-    for (int q = 0; q < kMaxRegBits; ++q) rmask |= L.r[q];
+    for (int q = 0; q < kMaxRegBits; ++q) rmask |= roff.r[q];
     if ((jrel & ~rmask) != 0u) return;
-    const int slot = fl->slot;
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
         if (i >= nreg) continue;
-        const bool hit = roff(L, i) == jrel;
+        const bool hit = roff(i) == jrel;
         if constexpr (KIND == 0) {
 #pragma unroll
             for (int n = 0; n < NV; ++n) {
@@ -656,43 +693,46 @@ __device__ __forceinline__ void element_op(const KArgs& a, T (&v)[NV][NR], const
     }
 }
 
+// The LDS slot at a byte offset.
+template <typename T>
+__device__ __forceinline__ T& lds_at(T* lds, unsigned off) {
+    return *reinterpret_cast<T*>(reinterpret_cast<char*>(lds) + off);
+}
+
 // Every stage of the pass on one tile held in registers, then the norm partial.
 template <typename R, int NV, int KMAX, int RB>
 __device__ __forceinline__ void compute_tile(const KArgs& a, const PK_CONST Pass* P, const PassCtx& C,
                                              int64_t tile, typename Cplx<R>::T (&v)[NV][1 << RB],
                                              const TileRefs<R>& U, typename Cplx<R>::T* lds, double* red) {
+    using T = typename Cplx<R>::T;
     constexpr int NT = 1 << (KMAX - RB);
     constexpr int NR = 1 << RB;
     const unsigned tid = threadIdx.x;
     const bool active = C.active;
     const int nreg = C.nreg;
     const PK_CONST Stage* S = cptr(a.stages) + P->stage_begin;
-    Layout L = C.L0;
+    Layout L = make_layout<(int)sizeof(T)>(load_head(S), tid);
     for (int s = 0; s < C.nstages; ++s, ++S) {
-        // one scalar word says which steps follow; only their parameters are loaded
-        const int steps = S->steps;
-        // the one-qubit steps' parameters (mat_pre_a .. mat_post) in two 16-byte loads
-        // issued with the step word, not one scalar round trip per step
-        typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-        const i32x4 sp0 = *reinterpret_cast<const PK_CONST i32x4*>(&S->mat_pre_a);
-        const i32x4 sp1 = *reinterpret_cast<const PK_CONST i32x4*>(&S->hmask2);
-        const int mat_pre_a = sp0.x, mat_pre = sp0.y, hmask1 = sp0.z, flip_mid = sp0.w;
-        const int hmask2 = sp1.x, mat_post_a = sp1.y, mat_post = sp1.z;
+        const i32x8 h = load_head(S);
+        const int steps = h[HD_STEPS];
+        const unsigned bits = (unsigned)h[HD_BITS];
         if (s > 0 && (steps & ST_EXCHANGE)) {
             // ---- LDS exchange: previous layout out, this layout in
-            const Layout Ln = (s == C.nstages - 1) ? C.Ll : make_layout<(int)sizeof(R) * 2>(S, C.nrb, tid);
+            const Layout Ln = make_layout<(int)sizeof(T)>(h, tid);
 #pragma unroll
             for (int n = 0; n < NV; ++n) {
                 if (active) {
+                    const RegBits po = reg_slots<(int)sizeof(T)>(L);
 #pragma unroll
                     for (int i = 0; i < NR; ++i)
-                        if (i < nreg) lds[L.pj ^ poff(L, i)] = v[n][i];
+                        if (i < nreg) lds_at(lds, L.pj ^ po(i)) = v[n][i];
                 }
                 __syncthreads();
                 if (active) {
+                    const RegBits pn = reg_slots<(int)sizeof(T)>(Ln);
 #pragma unroll
                     for (int i = 0; i < NR; ++i)
-                        if (i < nreg) v[n][i] = lds[Ln.pj ^ poff(Ln, i)];
+                        if (i < nreg) v[n][i] = lds_at(lds, Ln.pj ^ pn(i));
                 }
                 __syncthreads();
             }
@@ -700,30 +740,30 @@ __device__ __forceinline__ void compute_tile(const KArgs& a, const PK_CONST Pass
         }
         // ---- the sub-stage's steps, in their fixed order
         if constexpr (NV == 2) {
-            if (steps & ST_SEED) element_op<NV, NR, 2>(a, v, L, S->seed, tile, nreg, active);
+            if (steps & ST_SEED) element_op<NV, NR, 2>(a, v, L, S->head + HD_SEED, tile, nreg, active);
         }
-        if (steps & ST_FLIP_PRE) element_op<NV, NR, 0>(a, v, L, S->flip_pre, tile, nreg, active);
+        if (steps & ST_FLIP_PRE) element_op<NV, NR, 0>(a, v, L, S->head + HD_FLIP_PRE, tile, nreg, active);
         if (steps & ST_PHASE) apply_phases<NV, NR>(a, S, v, L, tile, U, active);
         if (steps & ST_MAT_PRE) {
             R m[8];
-            const PK_CONST double* mp = cptr(a.mats) + 8 * mat_pre;
+            const PK_CONST double* mp = cptr(a.mats) + 8 * h[HD_MAT_PRE];
 #pragma unroll
             for (int e = 0; e < 8; ++e) m[e] = (R)mp[e];
-            apply_mat<NV, NR>(v, mat_pre_a, m);
+            apply_mat<NV, NR>(v, (int)(bits >> 10 & 7u), m);
         }
-        if (steps & ST_H1) apply_hmask<NV, NR>(v, hmask1);
-        if (steps & ST_FLIP_MID) element_op<NV, NR, 0>(a, v, L, flip_mid, tile, nreg, active);
-        if (steps & ST_H2) apply_hmask<NV, NR>(v, hmask2);
+        if (steps & ST_H1) apply_hmask<NV, NR>(v, (int)(bits & 31u));
+        if (steps & ST_FLIP_MID) element_op<NV, NR, 0>(a, v, L, S->head + HD_FLIP_MID, tile, nreg, active);
+        if (steps & ST_H2) apply_hmask<NV, NR>(v, (int)(bits >> 5 & 31u));
         if (steps & ST_MAT_POST) {
             R m[8];
-            const PK_CONST double* mp = cptr(a.mats) + 8 * mat_post;
+            const PK_CONST double* mp = cptr(a.mats) + 8 * h[HD_MAT_POST];
 #pragma unroll
             for (int e = 0; e < 8; ++e) m[e] = (R)mp[e];
-            apply_mat<NV, NR>(v, mat_post_a, m);
+            apply_mat<NV, NR>(v, (int)(bits >> 13 & 7u), m);
         }
-        if ((steps & ST_MAT4) && active) op_mat4<NV, NR>(v, cptr(a.mats4) + 32 * S->mat4);
+        if ((steps & ST_MAT4) && active) op_mat4<NV, NR>(v, cptr(a.mats4) + 32 * S->head[HD_MAT4]);
         if constexpr (NR > 8)
-            if ((steps & ST_MAT4B) && active) op_mat4_hi<NV, NR>(v, cptr(a.mats4) + 32 * S->mat4b);
+            if ((steps & ST_MAT4B) && active) op_mat4_hi<NV, NR>(v, cptr(a.mats4) + 32 * S->head[HD_MAT4B]);
         if constexpr (NV == 2) {
             if (steps & ST_D2B) {
                 R mh[8];
@@ -731,7 +771,7 @@ __device__ __forceinline__ void compute_tile(const KArgs& a, const PK_CONST Pass
 #pragma unroll
                 for (int e = 0; e < 8; ++e) mh[e] = (R)mp[8 + e];
                 double g[3] = {0.0, 0.0, 0.0};
-                if (active) apply_d2bwd<NV, NR>(v, S->d2b_a, mh, mp + 16, g);
+                if (active) apply_d2bwd<NV, NR>(v, (int)(bits >> 16 & 7u), mh, mp + 16, g);
                 const double scale = 2.0 * (double)S->d2b_gscale;
                 const int gslot = S->d2b_gslot;
 #pragma unroll
@@ -762,7 +802,7 @@ __device__ __forceinline__ void compute_tile(const KArgs& a, const PK_CONST Pass
                     v[n][i].y *= sc;
                 }
         }
-        if (steps & ST_READ) element_op<NV, NR, 1>(a, v, L, S->read, tile, nreg, active);
+        if (steps & ST_READ) element_op<NV, NR, 1>(a, v, L, S->head + HD_READ, tile, nreg, active);
     }
 
     // ---- norm partial of the final state (FP64 for FP64 data; Neumaier-
@@ -810,15 +850,28 @@ __device__ __forceinline__ void run_tiles_ph(const KArgs& a, const PK_CONST Pass
                                              int64_t chunk) {
     using T = typename Cplx<R>::T;
     constexpr int NR = 1 << RB;
-    PassCtx C = make_ctx<(int)sizeof(R) * 2, RB>(a, P);
+    PassCtx C = make_ctx<KMAX, RB>(P);
     if constexpr (FULL) {
         C.active = true;
         C.nreg = NR;
         C.flags &= ~PASS_WIDE;
     }
     const int64_t off = P->state_off;
+    // the runs of the tile index: the first four stay in scalar registers
     const int nfrun = P->nfrun;
-    auto base_of = [&](int64_t t) { return off + deposit(t, P->frun, nfrun); };
+    uint32_t fm[4], fs[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        fm[q] = P->fmask[q];
+        fs[q] = P->fshift[q];
+    }
+    auto base_of = [&](int64_t t) {
+        int64_t r = off;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) r += (int64_t)((uint32_t)t & fm[q]) << fs[q];
+        for (int q = 4; q < nfrun; ++q) r += (int64_t)((uint32_t)t & P->fmask[q]) << P->fshift[q];
+        return r;
+    };
     auto refs_of = [&](int64_t t) { return PH ? load_refs<R>(a, P, t) : TileRefs<R>{(R)1, (R)0}; };
     // the workgroup's tiles come in runs of `chunk` consecutive ones, the runs
     // `stride` runs apart (chunk 1: every stride-th tile)
@@ -834,6 +887,7 @@ __device__ __forceinline__ void run_tiles_ph(const KArgs& a, const PK_CONST Pass
     if constexpr (NV == 2) {
         // two vectors already fill the register file: no second buffer
         int64_t j = 0;
+        warm_stages(a, P, C.nstages);
         for (int64_t tile = first; tile < ntiles; tile = next(tile, j)) {
             T v[NV][NR];
             const int64_t base = base_of(tile);
@@ -848,6 +902,7 @@ __device__ __forceinline__ void run_tiles_ph(const KArgs& a, const PK_CONST Pass
         int64_t basea = base_of(ta);
         TileRefs<R> ua = refs_of(ta);
         load_tile<R, 1, NR, NT>(a, C, basea, va);
+        warm_stages(a, P, C.nstages);
         for (;;) {
             int64_t jb = ja;
             const int64_t tb = next(ta, jb);
@@ -908,9 +963,12 @@ __device__ __forceinline__ void run_tiles(const KArgs& a, const PK_CONST Pass* P
 // ---------------------------------------------------------------------------- kernels
 
 // With 3 register bits the kernel is held to 128 VGPRs (four waves per SIMD): two
-// 2^12-tile workgroups of 512 threads then share a CU, as their LDS allows.
+// 2^12-tile workgroups of 512 threads then share a CU, as their LDS allows.  FP32 with
+// 5 is held to 256 (two waves per SIMD, two 2^13-tile workgroups a CU; 11 registers
+// spill): at 268 and one workgroup a CU an n_q = 25 iteration took 801 us, so 563.
 template <typename R, int NV, int KMAX, int RB>
-__global__ void __launch_bounds__(1 << (KMAX - RB)) __attribute__((amdgpu_waves_per_eu(RB == 3 ? 4 : 1)))
+__global__ void __launch_bounds__(1 << (KMAX - RB)) 
+    __attribute__((amdgpu_waves_per_eu(RB == 3 ? 4 : RB == 5 && sizeof(R) == 4 ? 2 : 1)))
 pass_kernel(KArgs a) {
     using T = typename Cplx<R>::T;
     __shared__ T lds[1 << KMAX];

@@ -331,6 +331,38 @@ void finish_sub(Stage& s, std::vector<PhaseOp>* table, std::vector<double>* twid
               (s.scale ? ST_SCALE : 0) | (s.read >= 0 ? ST_READ : 0) | (s.mat4b >= 0 ? ST_MAT4B : 0);
 }
 
+// The words of a sub-stage that the kernel reads together (Stage::head).
+void pack_head(Stage& s, const std::vector<Flip>& flips) {
+    std::memset(s.head, 0, sizeof s.head);
+    uint32_t rb = 0, rbs = 0;
+    for (int a = 0; a < kMaxRegBits; ++a) {
+        rb |= (uint32_t)(s.rb[a] < 0 ? 15 : s.rb[a]) << (4 * a);
+        rbs |= (uint32_t)(s.rbs[a] < 0 ? 15 : s.rbs[a]) << (4 * a);
+    }
+    auto bit = [](int a) { return (uint32_t)(a < 0 ? 7 : a); };
+    s.head[HD_STEPS] = s.steps;
+    s.head[HD_RB] = (int32_t)(rb | (uint32_t)s.nlanes << 24);
+    s.head[HD_RBS] = (int32_t)rbs;
+    s.head[HD_LANES] = (int32_t)s.lanes;
+    s.head[HD_LANES_REST] = (int32_t)s.lanes_rest;
+    s.head[HD_BITS] = (int32_t)((uint32_t)s.hmask1 | (uint32_t)s.hmask2 << 5 | bit(s.mat_pre_a) << 10 |
+                                bit(s.mat_post_a) << 13 | bit(s.d2b_a) << 16);
+    s.head[HD_MAT_PRE] = s.mat_pre;
+    s.head[HD_MAT_POST] = s.mat_post;
+    auto flip = [&](int word, int f, bool slot) {
+        if (f < 0) return;
+        s.head[word] = (int32_t)flips[f].tile;
+        s.head[word + 1] = flips[f].j;
+        if (slot) s.head[word + 2] = flips[f].slot;
+    };
+    flip(HD_FLIP_PRE, s.flip_pre, false);
+    flip(HD_FLIP_MID, s.flip_mid, false);
+    flip(HD_READ, s.read, true);
+    flip(HD_SEED, s.seed, true);
+    s.head[HD_MAT4] = s.mat4;
+    s.head[HD_MAT4B] = s.mat4b;
+}
+
 // A phase joins the accumulator slot of its register bits (the register bits of
 // its qubits in this layout), or opens a new one; its other local bits become
 // conditions on the thread's part of the label.
@@ -1379,50 +1411,47 @@ int recompile(Plan* plan, std::string* err) {
         p.part_base = hp.part_base;
         p.uref_begin = hp.uref_begin;
         p.nuref = hp.nuref;
-        p.kmax = hp.kmax;
-        p.rbits = hp.rbits;
-        for (int l = 0; l < 16; ++l) {
-            p.tpos[l] = l < hp.k ? hp.tbits[l] : -1;
-            p.stpos[l] = l < hp.k ? hp.sbits[l] : -1;
-        }
         std::vector<char> used(in.nq, 0);
         for (int b : hp.tbits) used[b] = 1;
         std::vector<int> fbits;
         for (int b = 0; b < in.nq; ++b)
             if (!used[b]) fbits.push_back(b);
-        // runs of consecutive positions: (source bit, length, destination bit)
-        auto runs = [](const std::vector<int>& pos, Run* out) {
-            int n = 0;
-            for (size_t i = 0; i < pos.size();) {
-                size_t j = i + 1;
-                while (j < pos.size() && pos[j] == pos[j - 1] + 1) ++j;
-                out[n].src = (int32_t)i;
-                out[n].len = (int32_t)(j - i);
-                out[n].dst = pos[i];
-                out[n].pad = 0;
-                ++n;
-                i = j;
-            }
-            return n;
-        };
-        p.ntrun = runs(hp.tbits, p.trun);
-        p.nstrun = runs(hp.sbits, p.strun);
-        p.nfrun = runs(fbits, p.frun);
-        // byte offsets of a thread inside a tile in the load / store layouts
+        // runs of consecutive free bits: bits i.. of the tile index go to fbits[i]..
+        for (size_t i = 0; i < fbits.size();) {
+            size_t j = i + 1;
+            while (j < fbits.size() && fbits[j] == fbits[j - 1] + 1) ++j;
+            p.fmask[p.nfrun] = (uint32_t)((((uint64_t)1 << (j - i)) - 1) << i);
+            p.fshift[p.nfrun] = (uint32_t)(fbits[i] - (int)i);
+            ++p.nfrun;
+            i = j;
+        }
+        // offsets of a thread inside a tile in the load / store layouts
         const int esz = plan->prec == PK_FP64 ? 16 : 8;
         for (int which = 0; which < 2; ++which) {
             const HostStage& hs = which == 0 ? hp.stages.front() : hp.stages.back();
             const std::vector<int>& pos = which == 0 ? hp.tbits : hp.sbits;
+            uint32_t* thr = which == 0 ? p.lthr : p.sthr;
+            uint32_t* rg = which == 0 ? p.lreg : p.sreg;
             uint64_t maxoff = 0;
+            int nthr = 0;
             for (int l = 0; l < hp.k; ++l) {
                 bool reg = false;
-                for (int a = 0; a < kMaxRegBits; ++a) reg = reg || hs.rb[a] == l;
-                if (!reg) maxoff += (uint64_t)1 << pos[l];
+                for (int a = 0; a < kMaxRegBits; ++a)
+                    if (hs.rb[a] == l) {
+                        reg = true;
+                        rg[a] = (uint32_t)1 << pos[l];
+                    }
+                if (reg) continue;
+                maxoff += (uint64_t)1 << pos[l];
+                thr[nthr++] = (uint32_t)1 << pos[l];
             }
             if (maxoff * (uint64_t)esz >= ((uint64_t)1 << 32)) p.flags |= PASS_WIDE;
         }
         p.nstages = (int)hp.subs.size();
-        for (const Stage& st : hp.subs) plan->stages.push_back(st);
+        for (Stage st : hp.subs) {
+            pack_head(st, plan->flips);
+            plan->stages.push_back(st);
+        }
         plan->passes.push_back(p);
     };
     for (size_t i = 0; i < plan->inst.size(); ++i)
@@ -1507,8 +1536,6 @@ TableLayout table_layout(const Plan* plan) {
     o = align256(o + plan->passes.size() * sizeof(Pass));
     t.stages = o;
     o = align256(o + plan->stages.size() * sizeof(Stage));
-    t.flips = o;
-    o = align256(o + plan->flips.size() * sizeof(Flip));
     t.phases = o;
     o = align256(o + plan->phases.size() * sizeof(PhaseOp));
     t.twid = o;
