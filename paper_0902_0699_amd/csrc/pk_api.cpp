@@ -195,6 +195,17 @@ PassLaunch base_launch(DevPlan* d, void* ws, int op) {
     return L;
 }
 
+// The fields of a launch that name pass `pass` of the plan's table.
+void set_pass(PassLaunch* L, const Plan& P, const HostPass& hp, int pass) {
+    L->pass = pass;
+    L->stage_begin = P.passes[pass].stage_begin;
+    L->nstages = P.passes[pass].nstages;
+    L->kmax = hp.kmax;
+    L->ntiles = hp.ntiles;
+    L->grid_cap = P.tiling.wgs_per_cu;
+    L->rbits = hp.rbits;
+}
+
 const double* angle_src(DevPlan* d, const double* angles) {
     if (angles) return angles;
     TableLayout t = table_layout(&d->host);
@@ -237,11 +248,7 @@ hipError_t enqueue_eval(DevPlan* d, const EvalArgs& a, hipStream_t st, std::vect
         L.src0 = r == 0 ? a.psi_in : a.psi_out;
         L.want_norm = a.norm_out != nullptr && r == reps - 1;
         for (size_t p = 0; p < in.fwd.size(); ++p) {
-            L.pass = (int)p;
-            L.kmax = in.fwd[p].kmax;
-            L.ntiles = in.fwd[p].ntiles;
-            L.grid_cap = P.tiling.wgs_per_cu;
-            L.rbits = in.fwd[p].rbits;
+            set_pass(&L, P, in.fwd[p], (int)p);
             if (ev) hipEventRecord((*ev)[2 * p], st);
             e = launch_pass(L, st);
             if (ev) hipEventRecord((*ev)[2 * p + 1], st);
@@ -318,11 +325,7 @@ hipError_t enqueue_passes(DevPlan* src, void* ws, const void* in, void* out, boo
     L.want_norm = want_norm;
     const Instance& inst = P.inst[0];
     for (size_t p = 0; p < inst.fwd.size(); ++p) {
-        L.pass = (int)p;
-        L.kmax = inst.fwd[p].kmax;
-        L.ntiles = inst.fwd[p].ntiles;
-        L.grid_cap = P.tiling.wgs_per_cu;
-        L.rbits = inst.fwd[p].rbits;
+        set_pass(&L, P, inst.fwd[p], (int)p);
         hipError_t e = launch_pass(L, st);
         if (e != hipSuccess) return e;
     }
@@ -459,11 +462,7 @@ hipError_t enqueue_backward(DevPlan* d, const BwdArgs& a, hipStream_t st) {
     L.nv = 2;
     const Instance& in = P.inst[0];
     for (size_t p = 0; p < in.bwd.size(); ++p) {
-        L.pass = P.n_fwd_passes + (int)p;
-        L.kmax = in.bwd[p].kmax;
-        L.ntiles = in.bwd[p].ntiles;
-        L.grid_cap = P.tiling.wgs_per_cu;
-        L.rbits = in.bwd[p].rbits;
+        set_pass(&L, P, in.bwd[p], P.n_fwd_passes + (int)p);
         e = launch_pass(L, st);
         if (e != hipSuccess) return e;
     }

@@ -28,6 +28,8 @@ struct KArgs {
     const double* dL;
     int32_t pass;
     int32_t want_norm;
+    int32_t stage_begin;  // of this pass (single-instance launches)
+    int32_t nstages;
 };
 
 // Sum of one double per thread over the workgroup; result valid in thread 0.

@@ -153,6 +153,8 @@ static KArgs kargs(const PassLaunch& L) {
     a.dL = L.dL;
     a.pass = L.pass;
     a.want_norm = L.want_norm;
+    a.stage_begin = L.stage_begin;
+    a.nstages = L.nstages;
     return a;
 }
 

@@ -24,6 +24,8 @@ struct PassLaunch {
     const double* dL;
     int32_t pass;
     int32_t want_norm;
+    int32_t stage_begin;  // first stage of the pass, and how many
+    int32_t nstages;
     int32_t kmax;
     int32_t nv;
     int32_t fp64;

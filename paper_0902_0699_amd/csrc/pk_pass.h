@@ -529,12 +529,13 @@ __device__ __forceinline__ PassCtx make_ctx(const PK_CONST Pass* P) {
     return C;
 }
 
-// Reads a line of each of the pass's first stages, all at the same time, so that the
-// tile loop finds their heads in the scalar cache (one after the other, each first
-// read would wait for memory).
-__device__ __forceinline__ void warm_stages(const KArgs& a, const PK_CONST Pass* P, int nstages) {
-    const PK_CONST Stage* S = cptr(a.stages) + P->stage_begin;
-    int32_t w = 0;
+// Reads a word of every line of the pass record that the tile loop uses, and of the
+// heads of its first stages, all at the same time: each read where it is first used
+// would wait for memory in turn.  A single-instance launch knows where the stages
+// start; a batched launch reads that from the record first.
+__device__ __forceinline__ void warm_pass(const KArgs& a, const PK_CONST Pass* P, int stage_begin, int nstages) {
+    const PK_CONST Stage* S = cptr(a.stages) + stage_begin;
+    int32_t w = P->flags ^ (int32_t)P->fmask[0] ^ (int32_t)P->fshift[0] ^ (int32_t)P->lthr[0] ^ (int32_t)P->sthr[0];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const PK_CONST Stage* Si = S + (i < nstages ? i : nstages - 1);
@@ -835,8 +836,10 @@ __device__ __forceinline__ void compute_tile(const KArgs& a, const PK_CONST Pass
 // Tiles first, first + stride, ... (below ntiles) of one pass.  With one vector, two register
 // buffers alternate: the next tile's HBM loads are issued before the current
 // tile's LDS stages, so memory traffic overlaps the exchange work of the one
-// workgroup an LDS-sized tile leaves per CU.  The prefetch is unconditional
-// (past the end it re-reads the current tile) so the wait counts stay static.
+// workgroup an LDS-sized tile leaves per CU.  In the FULL loop the prefetch is
+// unconditional (past the end it re-reads the current tile) so the wait counts stay
+// static; elsewhere they depend on the path anyway, and the last tile prefetches
+// nothing (a pass of one tile a workgroup read it twice).
 // PH: the pass has tile-part product tables, whose entries are loaded with the
 // tile's amplitudes.  NT: the pass streams (PASS_STREAM).  FULL: the tile fills
 // the workgroup (k == KMAX: every thread active, every register used) and lane
@@ -887,7 +890,6 @@ __device__ __forceinline__ void run_tiles_ph(const KArgs& a, const PK_CONST Pass
     if constexpr (NV == 2) {
         // two vectors already fill the register file: no second buffer
         int64_t j = 0;
-        warm_stages(a, P, C.nstages);
         for (int64_t tile = first; tile < ntiles; tile = next(tile, j)) {
             T v[NV][NR];
             const int64_t base = base_of(tile);
@@ -902,14 +904,13 @@ __device__ __forceinline__ void run_tiles_ph(const KArgs& a, const PK_CONST Pass
         int64_t basea = base_of(ta);
         TileRefs<R> ua = refs_of(ta);
         load_tile<R, 1, NR, NT>(a, C, basea, va);
-        warm_stages(a, P, C.nstages);
         for (;;) {
             int64_t jb = ja;
             const int64_t tb = next(ta, jb);
             const int64_t tbc = tb < ntiles ? tb : ta;
             const int64_t baseb = base_of(tbc);
             const TileRefs<R> ub = refs_of(tbc);
-            load_tile<R, 1, NR, NT>(a, C, baseb, vb);
+            if (FULL || tb < ntiles) load_tile<R, 1, NR, NT>(a, C, baseb, vb);
             compute_tile<R, 1, KMAX, RB>(a, P, C, ta, va, ua, lds, red);
             store_tile<R, 1, NR, NT>(a, C, basea, va);
             if (tb >= ntiles) break;
@@ -918,7 +919,7 @@ __device__ __forceinline__ void run_tiles_ph(const KArgs& a, const PK_CONST Pass
             const int64_t tcc = tc < ntiles ? tc : tb;
             const int64_t basec = base_of(tcc);
             ua = refs_of(tcc);
-            load_tile<R, 1, NR, NT>(a, C, basec, va);
+            if (FULL || tc < ntiles) load_tile<R, 1, NR, NT>(a, C, basec, va);
             compute_tile<R, 1, KMAX, RB>(a, P, C, tb, vb, ub, lds, red);
             store_tile<R, 1, NR, NT>(a, C, baseb, vb);
             if (tc >= ntiles) break;
@@ -974,6 +975,7 @@ pass_kernel(KArgs a) {
     __shared__ T lds[1 << KMAX];
     __shared__ double red[16];  // reduction scratch
     const PK_CONST Pass* P = cptr(a.passes) + a.pass;
+    warm_pass(a, P, a.stage_begin, a.nstages);
     const int64_t ntiles = P->ntiles;
     const int64_t G = gridDim.x;
     const int walk = P->walk;
@@ -1124,6 +1126,7 @@ __global__ void __launch_bounds__(1 << (KMAX - RB)) batched_kernel(KArgs a, Batc
         const PK_CONST InstDesc* D = idesc + inst;
         for (int p = 0; p < D->npass; ++p) {
             const PK_CONST Pass* P = cptr(a.passes) + D->first_pass + p;
+            warm_pass(a, P, P->stage_begin, P->nstages);
             run_tiles<R, 1, KMAX, RB>(a, P, 0, 1, P->ntiles, lds, red);
             // this workgroup's stores must be visible to its own loads of the next pass:
             // every wave waits for its stores to complete before the barrier
