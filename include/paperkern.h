@@ -259,8 +259,8 @@ int pk_workspace_bytes(const pk_plan* plan, int32_t op, int64_t* bytes);
  *   angles   device double[3 * n_rot] or NULL (n_rot = D2 and D4 gates; NULL = the
  *            angles given to pk_create)
  *   workspace device, >= pk_workspace_bytes(PK_OP_EVAL)
- * The launches are captured once into a hipGraph per pointer set and replayed.
- * Errors: PK_EINVAL (NULL/misaligned pointer, batched plan), PK_EDEVICE.
+ * The launches (one per pass, and one before them where `angles` are given) go to
+ * `stream` directly.  Errors: PK_EINVAL (NULL/misaligned pointer, batched plan), PK_EDEVICE.
  */
 int pk_evaluate(pk_plan* plan, const void* psi_in, void* psi_out, double* L_out, double* norm_out,
                 const double* angles, void* workspace, void* stream);
@@ -270,8 +270,8 @@ int pk_evaluate(pk_plan* plan, const void* psi_in, void* psi_out, double* L_out,
  * memory (code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc).  The same kernels as pk_evaluate, but their workspace is a
  * static device buffer of the library, PK_STATIC_WORKSPACE_BYTES per GPU (held
- * by each GPU the library runs on until the process ends), and the launches go
- * to `stream` directly: the call allocates nothing and builds no graph.
+ * by each GPU the library runs on until the process ends): the call allocates
+ * nothing and builds no graph.
  * Arguments as pk_evaluate, without `workspace`; the caller still owns
  * psi_in, psi_out, L_out and norm_out.
  * Set-up: the plan's tables must already be on the current device (any earlier
@@ -345,7 +345,7 @@ int pk_search_workspace_bytes(int64_t* bytes);
 
 /*
  * pk_evaluate_batched -- evaluate every instance of the plan ("multiverses",
- * Sec. 6.2) in one persistent launch replayed from a hipGraph.  States are
+ * Sec. 6.2) in one persistent launch (after one that clears its queue).  States are
  * packed at pk_plan_offsets(); L_out and norm_out (or NULL) hold n_inst doubles.
  * Other arguments as pk_evaluate.
  */

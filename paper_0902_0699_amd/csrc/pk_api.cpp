@@ -21,13 +21,11 @@ namespace {
 
 thread_local std::string g_error;
 
-enum GraphSlot { G_EVAL = 0, G_BATCH = 1, G_BWD = 2, G_REPEAT = 3, G_SLOTS = 4 };
-
 struct DevPlan {
     Plan host;
-    void* exec[G_SLOTS] = {nullptr, nullptr, nullptr, nullptr};
-    const void* key[G_SLOTS][8] = {};
-    hipStream_t cap = nullptr;
+    void* exec = nullptr;           // pk_evaluate_repeat's captured launches
+    const void* key[8] = {};        // and the arguments they were captured with
+    hipStream_t cap = nullptr;      // capture and set-up stream
     int n_cu = 0;
     unsigned batch_grid = 0;  // persistent grid of the batched launch
     uint64_t spin_ticks = 0;  // half a second of the device wall clock
@@ -71,13 +69,11 @@ bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) %
 
 void drop_device(DevPlan* d);
 
-// Captured graphs, and the fused repeat schedule (it copies the plan's settings).
+// The captured graph, and the fused repeat schedule (it copies the plan's settings).
 void drop_graphs(DevPlan* d) {
-    for (int s = 0; s < G_SLOTS; ++s) {
-        if (d->exec[s]) hipGraphExecDestroy(reinterpret_cast<hipGraphExec_t>(d->exec[s]));
-        d->exec[s] = nullptr;
-        std::memset(d->key[s], 0, sizeof d->key[s]);
-    }
+    if (d->exec) hipGraphExecDestroy(reinterpret_cast<hipGraphExec_t>(d->exec));
+    d->exec = nullptr;
+    std::memset(d->key, 0, sizeof d->key);
     if (d->fused) {
         drop_device(d->fused);
         if (d->fused->cap) hipStreamDestroy(d->fused->cap);
@@ -96,6 +92,24 @@ void drop_device(DevPlan* d) {
 template <typename T>
 void put(std::vector<char>& buf, size_t off, const std::vector<T>& v) {
     if (!v.empty()) std::memcpy(buf.data() + off, v.data(), v.size() * sizeof(T));
+}
+
+template <typename T>
+T* at(void* base, size_t off) {
+    return reinterpret_cast<T*>(reinterpret_cast<char*>(base) + off);
+}
+
+// The operators of a plan whose tables lie at `tables`.
+PrepArgs prep_args(const Plan& P, void* tables) {
+    TableLayout t = table_layout(&P);
+    PrepArgs p{};
+    p.smats = at<double>(tables, t.mats);
+    p.n_smats = (int32_t)P.static_mats.size();
+    p.smats4 = at<double>(tables, t.mats4);
+    p.n_smats4 = (int32_t)P.static_mats4.size();
+    p.params = at<ParamRef>(tables, t.params);
+    p.n_params = (int32_t)P.params.size();
+    return p;
 }
 
 int ensure_device(DevPlan* d) {
@@ -152,19 +166,29 @@ int ensure_device(DevPlan* d) {
         hipFree(ptr);
         return hip_fail(d, e, "hipMemcpy(plan tables)");
     }
+    if (!d->cap) {
+        e = hipStreamCreateWithFlags(&d->cap, hipStreamNonBlocking);
+        if (e != hipSuccess) {
+            hipFree(ptr);
+            return hip_fail(d, e, "hipStreamCreate");
+        }
+    }
+    // the matrices of a launch with the plan's own angles, by the kernel that builds
+    // them for other angles (the same values)
+    PrepArgs p = prep_args(P, ptr);
+    p.mats = at<double>(ptr, t.built);
+    p.mats4 = at<double>(ptr, t.built4);
+    p.angles = at<double>(ptr, t.mats + P.static_mats.size() * sizeof(double));
+    e = launch_prep(p, d->cap);
+    if (e == hipSuccess) e = hipStreamSynchronize(d->cap);
+    if (e != hipSuccess) {
+        hipFree(ptr);
+        return hip_fail(d, e, "plan matrices");
+    }
     P.d_tables = ptr;
     P.d_tables_bytes = t.total;
     P.device = dev;
-    if (!d->cap) {
-        e = hipStreamCreateWithFlags(&d->cap, hipStreamNonBlocking);
-        if (e != hipSuccess) return hip_fail(d, e, "hipStreamCreate");
-    }
     return PK_OK;
-}
-
-template <typename T>
-T* at(void* base, size_t off) {
-    return reinterpret_cast<T*>(reinterpret_cast<char*>(base) + off);
 }
 
 struct EvalArgs {
@@ -206,29 +230,45 @@ void set_pass(PassLaunch* L, const Plan& P, const HostPass& hp, int pass) {
     L->rbits = hp.rbits;
 }
 
-const double* angle_src(DevPlan* d, const double* angles) {
-    if (angles) return angles;
-    TableLayout t = table_layout(&d->host);
-    return at<double>(d->host.d_tables, t.mats + d->host.static_mats.size() * sizeof(double));
-}
+// Whether a launch takes the matrices the plan built when its tables were uploaded:
+// always, unless the call brings angles for rotations that the plan has.
+bool own_matrices(const DevPlan* d, const double* angles) { return !angles || d->host.params.empty(); }
 
-hipError_t enqueue_prep(DevPlan* d, void* ws, const double* angles, int op, int n_counters, hipStream_t st) {
+// Points the launch at its matrices, and builds them in the workspace first where the
+// call brings its own angles; clears n_counters launch counters (a launch of its own
+// only where there is something to build or clear).
+hipError_t enqueue_prep(DevPlan* d, PassLaunch* L, void* ws, const double* angles, int op, int n_counters,
+                        hipStream_t st) {
     Plan& P = d->host;
     TableLayout t = table_layout(&P);
     WsLayout w = workspace_layout(&P, op);
-    PrepArgs p{};
+    PrepArgs p = prep_args(P, P.d_tables);
+    if (own_matrices(d, angles)) {
+        L->mats = at<double>(P.d_tables, t.built);
+        L->mats4 = at<double>(P.d_tables, t.built4);
+        if (n_counters == 0) return hipSuccess;
+        p.n_smats = p.n_smats4 = p.n_params = 0;
+    }
     p.mats = at<double>(ws, w.mats);
-    p.smats = at<double>(P.d_tables, t.mats);
-    p.n_smats = (int32_t)P.static_mats.size();
     p.mats4 = at<double>(ws, w.mats4);
-    p.smats4 = at<double>(P.d_tables, t.mats4);
-    p.n_smats4 = (int32_t)P.static_mats4.size();
-    p.angles = angle_src(d, angles);
-    p.params = at<ParamRef>(P.d_tables, t.params);
-    p.n_params = (int32_t)P.params.size();
+    p.angles = angles;
     p.counters = at<unsigned int>(ws, w.counters);
     p.n_counters = n_counters;
     return launch_prep(p, st);
+}
+
+// The largest number of tiles whose norm partials the last pass combines itself: up to
+// it, the launch saved (~5 us) costs less than one workgroup's reading them.
+constexpr int64_t kSelfCombine = 4096;
+
+// Has the pass that launches next combine L and the norm of `P` itself, where it may.
+bool self_combine(PassLaunch* L, const Plan& P, double* L_out, double* norm_out) {
+    if (P.inst[0].fwd.back().ntiles > kSelfCombine) return false;
+    L->ticket = at<unsigned int>(P.d_tables, table_layout(&P).ticket);
+    L->L_out = L_out;
+    L->norm_out = norm_out;
+    L->n_reads = (int32_t)P.inst[0].marked.size();
+    return true;
 }
 
 // Evaluation of a single-instance plan: prep, every forward pass, final combine.
@@ -238,9 +278,10 @@ hipError_t enqueue_prep(DevPlan* d, void* ws, const double* angles, int op, int 
 hipError_t enqueue_eval(DevPlan* d, const EvalArgs& a, hipStream_t st, std::vector<hipEvent_t>* ev,
                         int64_t reps = 1) {
     Plan& P = d->host;
-    hipError_t e = enqueue_prep(d, a.ws, a.angles, PK_OP_EVAL, 0, st);
-    if (e != hipSuccess) return e;
     PassLaunch L = base_launch(d, a.ws, PK_OP_EVAL);
+    hipError_t e = enqueue_prep(d, &L, a.ws, a.angles, PK_OP_EVAL, 0, st);
+    if (e != hipSuccess) return e;
+    bool combined = false;
     L.dst0 = a.psi_out;
     L.nv = 1;
     const Instance& in = P.inst[0];
@@ -249,12 +290,14 @@ hipError_t enqueue_eval(DevPlan* d, const EvalArgs& a, hipStream_t st, std::vect
         L.want_norm = a.norm_out != nullptr && r == reps - 1;
         for (size_t p = 0; p < in.fwd.size(); ++p) {
             set_pass(&L, P, in.fwd[p], (int)p);
+            if (r == reps - 1 && p + 1 == in.fwd.size()) combined = self_combine(&L, P, a.L_out, a.norm_out);
             if (ev) hipEventRecord((*ev)[2 * p], st);
             e = launch_pass(L, st);
             if (ev) hipEventRecord((*ev)[2 * p + 1], st);
             if (e != hipSuccess) return e;
         }
     }
+    if (combined) return hipSuccess;
     TableLayout t = table_layout(&P);
     return launch_reduce(at<Reduction>(P.d_tables, t.red), 2 * (int)P.inst.size(), static_cast<double*>(a.ws),
                          a.L_out, a.norm_out, nullptr, st);
@@ -319,6 +362,7 @@ RepeatSplit repeat_split(DevPlan* d, int64_t reps) {
 hipError_t enqueue_passes(DevPlan* src, void* ws, const void* in, void* out, bool want_norm, hipStream_t st) {
     Plan& P = src->host;
     PassLaunch L = base_launch(src, ws, PK_OP_EVAL);
+    enqueue_prep(src, &L, ws, nullptr, PK_OP_EVAL, 0, st);  // the plan's own matrices: no launch
     L.src0 = in;
     L.dst0 = out;
     L.nv = 1;
@@ -335,8 +379,7 @@ hipError_t enqueue_passes(DevPlan* src, void* ws, const void* in, void* out, boo
 // pk_evaluate_repeat with the fused schedule: prep, the single applications, the
 // fused rounds, then the final combine of the last one (same workspace layout).
 hipError_t enqueue_repeat_fused(DevPlan* d, const RepeatSplit& sp, const EvalArgs& a, hipStream_t st) {
-    hipError_t e = enqueue_prep(d, a.ws, a.angles, PK_OP_EVAL, 0, st);
-    if (e != hipSuccess) return e;
+    hipError_t e = hipSuccess;
     int64_t done = 0;
     for (int64_t r = 0; r < sp.single; ++r, ++done) {
         e = enqueue_passes(d, a.ws, done == 0 ? a.psi_in : a.psi_out, a.psi_out, false, st);
@@ -381,9 +424,9 @@ unsigned repeat_grid(DevPlan* d) {
 // prep (clears the barrier counter), the persistent launch, the final combine.
 hipError_t enqueue_repeat(DevPlan* d, const EvalArgs& a, hipStream_t st, int64_t reps, unsigned grid) {
     Plan& P = d->host;
-    hipError_t e = enqueue_prep(d, a.ws, a.angles, PK_OP_EVAL, 64, st);  // arrival counter and release word
-    if (e != hipSuccess) return e;
     PassLaunch L = base_launch(d, a.ws, PK_OP_EVAL);
+    hipError_t e = enqueue_prep(d, &L, a.ws, a.angles, PK_OP_EVAL, 64, st);  // arrival counter and release word
+    if (e != hipSuccess) return e;
     const Instance& in = P.inst[0];
     L.src0 = a.psi_in;
     L.dst0 = a.psi_out;
@@ -411,9 +454,9 @@ hipError_t enqueue_repeat(DevPlan* d, const EvalArgs& a, hipStream_t st, int64_t
 hipError_t enqueue_batched(DevPlan* d, const EvalArgs& a, hipStream_t st) {
     Plan& P = d->host;
     const TeamSchedule& ts = P.team;
-    hipError_t e = enqueue_prep(d, a.ws, a.angles, PK_OP_EVAL, 2 + ts.n_teams, st);
-    if (e != hipSuccess) return e;
     PassLaunch L = base_launch(d, a.ws, PK_OP_EVAL);
+    hipError_t e = enqueue_prep(d, &L, a.ws, a.angles, PK_OP_EVAL, 2 + ts.n_teams, st);
+    if (e != hipSuccess) return e;
     L.src0 = a.psi_in;
     L.dst0 = a.psi_out;
     L.want_norm = a.norm_out != nullptr;
@@ -450,10 +493,10 @@ struct BwdArgs {
 
 hipError_t enqueue_backward(DevPlan* d, const BwdArgs& a, hipStream_t st) {
     Plan& P = d->host;
-    hipError_t e = enqueue_prep(d, a.ws, a.angles, PK_OP_BACKWARD, 0, st);
-    if (e != hipSuccess) return e;
     WsLayout w = workspace_layout(&P, PK_OP_BACKWARD);
     PassLaunch L = base_launch(d, a.ws, PK_OP_BACKWARD);
+    hipError_t e = enqueue_prep(d, &L, a.ws, a.angles, PK_OP_BACKWARD, 0, st);
+    if (e != hipSuccess) return e;
     L.src0 = a.psi_out;
     L.dst0 = at<void>(a.ws, w.state);
     L.dst1 = a.grad_psi;
@@ -477,17 +520,26 @@ bool no_graph() {
     return v && v[0] && v[0] != '0';
 }
 
-// Replays the cached graph for `slot` when the pointer set matches, else
-// captures `fn` on the plan's capture stream and instantiates it.
+// Launches `fn` on the stream.  A call of a few launches goes to the stream directly:
+// 9 us of host time for three (n_q = 12), where replaying their graph took 22 us and
+// capturing it anew, for buffers it has not seen, 49 us.
 template <typename Fn>
-int run_graphed(DevPlan* d, int slot, const void* const (&key)[8], hipStream_t st, Fn fn) {
+int run_direct(DevPlan* d, hipStream_t st, Fn fn) {
+    hipError_t e = fn(st);
+    return e == hipSuccess ? PK_OK : hip_fail(d, e, "kernel launch");
+}
+
+// Replays the cached graph when its arguments match, else captures `fn` on the
+// plan's capture stream and instantiates it.
+template <typename Fn>
+int run_graphed(DevPlan* d, const void* const (&key)[8], hipStream_t st, Fn fn) {
     if (no_graph()) {
         hipError_t e = fn(st);
         return e == hipSuccess ? PK_OK : hip_fail(d, e, "kernel launch");
     }
-    if (!d->exec[slot] || std::memcmp(d->key[slot], key, sizeof key) != 0) {
-        if (d->exec[slot]) hipGraphExecDestroy(reinterpret_cast<hipGraphExec_t>(d->exec[slot]));
-        d->exec[slot] = nullptr;
+    if (!d->exec || std::memcmp(d->key, key, sizeof key) != 0) {
+        if (d->exec) hipGraphExecDestroy(reinterpret_cast<hipGraphExec_t>(d->exec));
+        d->exec = nullptr;
         hipError_t e = hipStreamBeginCapture(d->cap, hipStreamCaptureModeThreadLocal);
         if (e != hipSuccess) return hip_fail(d, e, "hipStreamBeginCapture");
         hipError_t le = fn(d->cap);
@@ -502,10 +554,10 @@ int run_graphed(DevPlan* d, int slot, const void* const (&key)[8], hipStream_t s
         e = hipGraphInstantiate(&ex, g, nullptr, nullptr, 0);
         hipGraphDestroy(g);
         if (e != hipSuccess) return hip_fail(d, e, "hipGraphInstantiate");
-        d->exec[slot] = ex;
-        std::memcpy(d->key[slot], key, sizeof key);
+        d->exec = ex;
+        std::memcpy(d->key, key, sizeof key);
     }
-    hipError_t e = hipGraphLaunch(reinterpret_cast<hipGraphExec_t>(d->exec[slot]), st);
+    hipError_t e = hipGraphLaunch(reinterpret_cast<hipGraphExec_t>(d->exec), st);
     return e == hipSuccess ? PK_OK : hip_fail(d, e, "hipGraphLaunch");
 }
 
@@ -767,9 +819,8 @@ int pk_evaluate(pk_plan* plan, const void* psi_in, void* psi_out, double* L_out,
     rc = ensure_device(d);
     if (rc != PK_OK) return rc;
     EvalArgs a{psi_in, psi_out, L_out, norm_out, angles, workspace};
-    const void* const key[8] = {psi_in, psi_out, L_out, norm_out, angles, workspace, nullptr, nullptr};
-    return run_graphed(d, G_EVAL, key, static_cast<hipStream_t>(stream),
-                       [&](hipStream_t s) { return enqueue_eval(d, a, s, nullptr); });
+    return run_direct(d, static_cast<hipStream_t>(stream),
+                      [&](hipStream_t s) { return enqueue_eval(d, a, s, nullptr); });
 }
 
 int pk_evaluate_static(pk_plan* plan, const void* psi_in, void* psi_out, double* L_out, double* norm_out,
@@ -817,16 +868,16 @@ int pk_evaluate_repeat(pk_plan* plan, int64_t reps, const void* psi_in, void* ps
                                 reinterpret_cast<const void*>((intptr_t)reps),
                                 reinterpret_cast<const void*>((intptr_t)grid)};
     if (grid > 0)
-        return run_graphed(d, G_REPEAT, key, static_cast<hipStream_t>(stream),
+        return run_graphed(d, key, static_cast<hipStream_t>(stream),
                            [&](hipStream_t s) { return enqueue_repeat(d, a, s, reps, grid); });
     const RepeatSplit sp = repeat_split(d, reps);
     if (sp.fused) {
         rc = ensure_device(sp.fused);
         if (rc != PK_OK) return fail(d, rc, sp.fused->host.last_error);
-        return run_graphed(d, G_REPEAT, key, static_cast<hipStream_t>(stream),
+        return run_graphed(d, key, static_cast<hipStream_t>(stream),
                            [&](hipStream_t s) { return enqueue_repeat_fused(d, sp, a, s); });
     }
-    return run_graphed(d, G_REPEAT, key, static_cast<hipStream_t>(stream),
+    return run_graphed(d, key, static_cast<hipStream_t>(stream),
                        [&](hipStream_t s) { return enqueue_eval(d, a, s, nullptr, reps); });
 }
 
@@ -882,9 +933,7 @@ int pk_evaluate_batched(pk_plan* plan, const void* psi_in, void* psi_out, double
     rc = ensure_device(d);
     if (rc != PK_OK) return rc;
     EvalArgs a{psi_in, psi_out, L_out, norm_out, angles, workspace};
-    const void* const key[8] = {psi_in, psi_out, L_out, norm_out, angles, workspace, nullptr, nullptr};
-    return run_graphed(d, G_BATCH, key, static_cast<hipStream_t>(stream),
-                       [&](hipStream_t s) { return enqueue_batched(d, a, s); });
+    return run_direct(d, static_cast<hipStream_t>(stream), [&](hipStream_t s) { return enqueue_batched(d, a, s); });
 }
 
 int pk_backward(pk_plan* plan, const void* psi_out, const double* dL, void* grad_psi_in, double* grad_angles,
@@ -901,9 +950,7 @@ int pk_backward(pk_plan* plan, const void* psi_out, const double* dL, void* grad
     int rc = ensure_device(d);
     if (rc != PK_OK) return rc;
     BwdArgs a{psi_out, dL, grad_psi_in, grad_angles, angles, workspace};
-    const void* const key[8] = {psi_out, dL, grad_psi_in, grad_angles, angles, workspace, nullptr, nullptr};
-    return run_graphed(d, G_BWD, key, static_cast<hipStream_t>(stream),
-                       [&](hipStream_t s) { return enqueue_backward(d, a, s); });
+    return run_direct(d, static_cast<hipStream_t>(stream), [&](hipStream_t s) { return enqueue_backward(d, a, s); });
 }
 
 int pk_pair_indices(int32_t nq, int32_t i_s, int64_t first, int64_t count, int64_t* n0, int64_t* n1,

@@ -155,6 +155,10 @@ static KArgs kargs(const PassLaunch& L) {
     a.want_norm = L.want_norm;
     a.stage_begin = L.stage_begin;
     a.nstages = L.nstages;
+    a.ticket = L.ticket;
+    a.L_out = L.L_out;
+    a.norm_out = L.norm_out;
+    a.n_reads = L.n_reads;
     return a;
 }
 

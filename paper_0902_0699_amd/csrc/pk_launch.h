@@ -31,6 +31,10 @@ struct PassLaunch {
     int32_t fp64;
     int32_t rbits;     // register bits per thread (4 or 5)
     int64_t ntiles;
+    unsigned int* ticket;  // not null: the pass combines L_out and norm_out itself (see KArgs)
+    double* L_out;
+    double* norm_out;
+    int32_t n_reads;
     int64_t grid_cap;  // workgroups per CU of a pass launch; 0 = as many as fit
 };
 

@@ -656,6 +656,15 @@ __device__ __forceinline__ void store_tile(const KArgs& a, const PassCtx& C, int
     }
 }
 
+// Stores a readout or norm partial; where the pass itself combines them (KArgs::ticket)
+// past the caches of this XCD, to where the combining workgroup reads it.
+__device__ __forceinline__ void publish(const KArgs& a, double* p, double x) {
+    if (a.ticket)
+        __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else
+        *p = x;
+}
+
 // One-amplitude steps on the element el (tile, local label, slot) when it lies in this
 // tile and thread: KIND 0 negates it (Oracle, Inv's C_0), 1 stores |C|^2 to its readout
 // slot, 2 seeds lambda = dL * psi there.  Written as selects, so the register
@@ -684,7 +693,7 @@ __device__ __forceinline__ void element_op(const KArgs& a, T (&v)[NV][NR], const
         } else if constexpr (KIND == 1) {
             if (hit) {
                 const double x = v[0][i].x, y = v[0][i].y;
-                a.reads[slot] = x * x + y * y;
+                publish(a, a.reads + slot, x * x + y * y);
             }
         } else if constexpr (NV == 2) {
             const auto d = (decltype(v[0][0].x))a.dL[slot];
@@ -829,7 +838,7 @@ __device__ __forceinline__ void compute_tile(const KArgs& a, const PK_CONST Pass
             }
         }
         const double tot = block_sum<NT>(part, red);
-        if (tid == 0) a.partials[P->part_base + tile] = tot;
+        if (tid == 0) publish(a, a.partials + P->part_base + tile, tot);
     }
 }
 
@@ -963,6 +972,55 @@ __device__ __forceinline__ void run_tiles(const KArgs& a, const PK_CONST Pass* P
 
 // ---------------------------------------------------------------------------- kernels
 
+// Sum of `count` doubles, added as reduce_kernel does with its 256 threads (thread t
+// adds entries t, t + 256, ..., then butterflies and the waves in order), whatever the
+// workgroup's size; valid in thread 0.
+template <int NT>
+__device__ __forceinline__ double combine(const double* src, int64_t count, double* red) {
+    constexpr int nw = NT / 64;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int vw = wave; vw < 4; vw += nw) {
+        double s = 0.0;
+        const int64_t t0 = vw * 64 + lane;
+#pragma unroll 4
+        for (int64_t t = t0; t < count; t += 256)
+            s += __hip_atomic_load(src + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+        if (lane == 0) red[vw] = s;
+    }
+    __syncthreads();
+    const double tot = ((red[0] + red[1]) + red[2]) + red[3];
+    __syncthreads();
+    return tot;
+}
+
+// L and the norm of a single instance, by the workgroup of its last pass that finishes
+// last (a ticket counts them; it ends at zero, as it started, for the next launch).
+// Every readout and partial was stored past the caches (publish) and has completed
+// when its wave gets here, so no cache is written back or invalidated for it: the
+// fences that would do so cost a grid barrier ~9 us, a combining launch ~5 us.
+template <int NT>
+__device__ __forceinline__ void finish_single(const KArgs& a, const PK_CONST Pass* P, double* red) {
+    __shared__ int last;
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (threadIdx.x == 0)
+        last = gridDim.x == 1 ||
+               __hip_atomic_fetch_add(a.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+    __syncthreads();
+    if (!last) return;
+    const double L = combine<NT>(a.reads, a.n_reads, red);
+    if (threadIdx.x == 0) {
+        *a.L_out = L;
+        if (gridDim.x > 1) __hip_atomic_store(a.ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (a.want_norm) {
+        const double norm = combine<NT>(a.partials + P->part_base, P->ntiles, red);
+        if (threadIdx.x == 0) *a.norm_out = norm;
+    }
+}
+
 // With 3 register bits the kernel is held to 128 VGPRs (four waves per SIMD): two
 // 2^12-tile workgroups of 512 threads then share a CU, as their LDS allows.  FP32 with
 // 5 is held to 256 (two waves per SIMD, two 2^13-tile workgroups a CU; 11 registers
@@ -988,6 +1046,8 @@ pass_kernel(KArgs a) {
         const int64_t c = walk > 0 ? walk : (ntiles + G - 1) / G;
         run_tiles<R, NV, KMAX, RB, true>(a, P, (int64_t)blockIdx.x * c, G, ntiles, lds, red, c);
     }
+    if constexpr (NV == 1)
+        if (a.ticket) finish_single<(1 << (KMAX - RB))>(a, P, red);
 }
 
 // Team barrier of the batched launch: every member adds one to the team's

@@ -1558,6 +1558,12 @@ TableLayout table_layout(const Plan* plan) {
     o = align256(o + plan->inst.size() * sizeof(int32_t));
     t.red = o;  // evaluation reductions, then backward reductions
     o = align256(o + (2 * plan->inst.size() + 3 * plan->d2_grad.size()) * sizeof(Reduction));
+    t.built = o;  // every matrix of a launch with the plan's own angles (see PrepArgs)
+    o = align256(o + (size_t)(2 * plan->n_static + 5 * plan->n_d2) * 8 * sizeof(double));
+    t.built4 = o;
+    o = align256(o + (size_t)(2 * plan->n_static4 + 5 * plan->n_d4) * 32 * sizeof(double));
+    t.ticket = o;  // workgroups done of a last pass that combines its readouts
+    o = align256(o + sizeof(uint32_t));
     t.total = std::max<size_t>(o, 256);
     return t;
 }
