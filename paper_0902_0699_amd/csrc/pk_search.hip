@@ -5,12 +5,21 @@
 // 2|0><0| - I (Eq. inversion) and HALL|0..0> = |s>, the uniform state (Eq.
 // Shor1), HALL . Inv . HALL = 2|s><s| - I, so
 //     (G C)_n = 2 m - (O C)_n,   m = mean over n of (O C)_n,
-// where O flips the marked amplitudes.  A step is then one streaming pass: read
-// C, write 2m - C, and sum the written values block by block for the next mean.
-// The marked labels (a handful) are fixed afterwards by a one-workgroup kernel:
-// the pass wrote w_x = 2m - C_x where 2m + C_x was due, so c_x = 4m - w_x, and the
-// next mean is (sum of the pass - 4 m |M|) / N, since w_x + c_x = 4m.  Sums are
-// FP64 (also for FP32 states) in a fixed order.
+// where O flips the marked amplitudes.  Every unmarked amplitude thus changes sign
+// and takes the same addend, every marked one takes the same addend without the
+// sign: after k iterations
+//     C_n -> (-1)^k C_n + a   (n not marked),     C_x -> C_x + b   (x marked).
+// The two addends follow from the sums U over the unmarked and V over the marked
+// amplitudes.  With |M| marked of N, the pair (U / sqrt(N - |M|), V / sqrt|M|) is
+// rotated by one iteration through the angle t = 2 asin(sqrt(|M| / N)):
+//     cos t = 1 - 2 |M| / N,   sin t = 2 sqrt(|M| (N - |M|)) / N
+// (substitute m = (U - V) / N into U' = 2 m (N - |M|) - U and V' = V + 2 m |M|), so
+// U and V after k iterations are the pair rotated by k t, and
+//     a = (U_k - (-1)^k U) / (N - |M|),   b = (V_k - V) / |M|.
+// The state is read once for U and read and written once for the result, whatever
+// k is; all of it in FP64 (also for FP32 states), sums in a fixed order.  Iteration by
+// iteration (one pass and one combining launch each), the n_q = 20 search took 8.46
+// ms; this takes 21 us, three launches' latency.
 #include <hip/hip_runtime.h>
 
 #include "pk_launch.h"
@@ -52,6 +61,7 @@ template <typename T>
 __global__ void __launch_bounds__(kThreads) sum_kernel(const T* src, int64_t n, int64_t chunk, double2* part) {
     const int64_t lo = (int64_t)blockIdx.x * chunk, hi = lo + chunk < n ? lo + chunk : n;
     double2 acc = {0.0, 0.0};
+#pragma unroll 4
     for (int64_t e = lo + threadIdx.x; e < hi; e += kThreads) {
         const double2 v = wide(src[e]);
         acc.x += v.x;
@@ -60,95 +70,201 @@ __global__ void __launch_bounds__(kThreads) sum_kernel(const T* src, int64_t n, 
     block_sum2(acc, part);
 }
 
-template <typename T>
-__global__ void __launch_bounds__(kThreads) diffuse_kernel(const T* src, T* dst, int64_t n, int64_t chunk,
-                                                           const double2* mean, double2* part) {
-    using R = decltype(src[0].x);
-    const double2 m = *mean;
-    const R mx = (R)(2.0 * m.x), my = (R)(2.0 * m.y);
-    const int64_t lo = (int64_t)blockIdx.x * chunk, hi = lo + chunk < n ? lo + chunk : n;
-    double2 acc = {0.0, 0.0};
-    for (int64_t e = lo + threadIdx.x; e < hi; e += kThreads) {
-        const T v = src[e];
-        T w;
-        w.x = mx - v.x;
-        w.y = my - v.y;
-        dst[e] = w;
-        acc.x += (double)w.x;
-        acc.y += (double)w.y;
+// The addends of k iterations from the sum over every amplitude and the sum over the
+// marked ones.
+struct Addends {
+    double2 a, b;
+};
+
+__device__ __forceinline__ Addends addends(double2 sum, double2 V, int64_t n, int count, int64_t k) {
+    const double N = (double)n, M = (double)count, K = N - M, odd = (k & 1) ? 1.0 : 0.0;
+    const double2 U = {sum.x - V.x, sum.y - V.y};
+    Addends r;
+    if (count == 0) {  // the mean does not change
+        r.a = double2{odd * 2.0 * (U.x / N), odd * 2.0 * (U.y / N)};
+        r.b = double2{0.0, 0.0};
+        return r;
     }
-    block_sum2(acc, part);
+    if (count == n) {  // m = -V / N, the sign of V alternates
+        r.a = double2{0.0, 0.0};
+        r.b = double2{-odd * 2.0 * (V.x / N), -odd * 2.0 * (V.y / N)};
+        return r;
+    }
+    double sn, cs;
+    sincos((double)k * (2.0 * asin(sqrt(M / N))), &sn, &cs);
+    const double g = sqrt(K / M), sign = (k & 1) ? -1.0 : 1.0;
+    // U_k = cos U - sin g V and V_k = cos V + sin U / g
+    r.a = double2{((cs - sign) * U.x - sn * g * V.x) / K, ((cs - sign) * U.y - sn * g * V.y) / K};
+    r.b = double2{((cs - 1.0) * V.x + sn / g * U.x) / M, ((cs - 1.0) * V.y + sn / g * U.y) / M};
+    // from the second iteration on, the mean of a non-finite part is NaN
+    if (k > 1 && !isfinite(sum.x)) r.a.x = r.b.x = __builtin_nan("");
+    if (k > 1 && !isfinite(sum.y)) r.a.y = r.b.y = __builtin_nan("");
+    return r;
 }
 
-// mode 0 (start): m = (sum - 2 sum_x C_x) / N, the mean of O psi_in.
-// mode 1 (after a pass): c_x = 4 m - w_x at the marked labels; m' = (sum - 4 m |M|) / N;
-//                        L = sum_x |c_x|^2.
 template <typename T>
-__global__ void __launch_bounds__(kThreads) combine_kernel(const double2* part, int nparts, MarkedSet ms, T* state,
-                                                           int64_t n, double2* mean, double* L, int mode) {
-    using R = decltype(state[0].x);
-    // the partial sums: lane l adds parts l, l + 64, ..., then a butterfly (fixed order);
+__device__ __forceinline__ T plus(const T& v, double sign, const double2& add) {
+    using R = decltype(v.x);
+    T w;
+    w.x = (R)(sign * (double)v.x + add.x);
+    w.y = (R)(sign * (double)v.y + add.y);
+    return w;
+}
+
+// One workgroup: the block sums added in order (lane l adds parts l, l + 64, ..., then
+// a butterfly), the addends, and L = sum_x |C_x + b|^2 of the values that
+// apply_kernel will store.
+template <typename T>
+__global__ void __launch_bounds__(64) combine_kernel(const double2* part, int nparts, MarkedSet ms, const T* src,
+                                                     int64_t n, int64_t k, double2* add, double* L) {
     // all of a lane's loads are issued before the first add, so their latencies overlap
     constexpr int kPer = kGrid / 64;
+    const int lane = threadIdx.x;
+    T own{0, 0};
+    if (lane < ms.count) own = src[ms.label[lane]];
     double2 pv[kPer];
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
-        const int b = threadIdx.x + 64 * j;
+        const int b = lane + 64 * j;
         pv[j] = b < nparts ? part[b] : double2{0.0, 0.0};
     }
     double2 s = {0.0, 0.0};
 #pragma unroll
     for (int j = 0; j < kPer; ++j)
-        if (threadIdx.x + 64 * j < nparts) {
+        if (lane + 64 * j < nparts) {
             s.x += pv[j].x;
             s.y += pv[j].y;
         }
+    double2 v = wide(own);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
         s.x += __shfl_xor(s.x, off, 64);
         s.y += __shfl_xor(s.y, off, 64);
+        v.x += __shfl_xor(v.x, off, 64);
+        v.y += __shfl_xor(v.y, off, 64);
     }
-    if (threadIdx.x != 0) return;
-    const double2 m = *mean;
-    double l = 0.0;
-    if (mode == 0) {
-        for (int i = 0; i < ms.count; ++i) {
-            const double2 c = wide(state[ms.label[i]]);
-            s.x -= 2.0 * c.x;
-            s.y -= 2.0 * c.y;
-            l += c.x * c.x + c.y * c.y;
-        }
+    const Addends r = addends(s, v, n, ms.count, k);
+    const double2 c = wide(plus(own, 1.0, r.b));
+    double l = lane < ms.count ? c.x * c.x + c.y * c.y : 0.0;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off, 64);
+    if (lane == 0) {
+        add[0] = r.a;
+        add[1] = r.b;
+        *L = l;
+    }
+}
+
+// The result, chunk by chunk; only a chunk that holds marked labels looks for them.
+template <typename T>
+__global__ void __launch_bounds__(kThreads) apply_kernel(const T* src, T* dst, int64_t n, int64_t chunk, double sign,
+                                                         const double2* add, MarkedSet ms) {
+    const double2 a = add[0], b = add[1];
+    const int64_t lo = (int64_t)blockIdx.x * chunk, hi = lo + chunk < n ? lo + chunk : n;
+    bool any = false;
+    for (int i = 0; i < ms.count; ++i) any = any || (ms.label[i] >= lo && ms.label[i] < hi);
+    if (!any) {
+#pragma unroll 4
+        for (int64_t e = lo + threadIdx.x; e < hi; e += kThreads) dst[e] = plus(src[e], sign, a);
     } else {
-        for (int i = 0; i < ms.count; ++i) {
-            const double2 w = wide(state[ms.label[i]]);
-            T c;
-            c.x = (R)(4.0 * m.x - w.x);
-            c.y = (R)(4.0 * m.y - w.y);
-            state[ms.label[i]] = c;
-            l += (double)c.x * (double)c.x + (double)c.y * (double)c.y;
+        for (int64_t e = lo + threadIdx.x; e < hi; e += kThreads) {
+            bool marked = false;
+            for (int i = 0; i < ms.count; ++i) marked = marked || e == ms.label[i];
+            dst[e] = marked ? plus(src[e], 1.0, b) : plus(src[e], sign, a);
         }
-        s.x -= 4.0 * m.x * ms.count;
-        s.y -= 4.0 * m.y * ms.count;
     }
-    *mean = double2{s.x / (double)n, s.y / (double)n};
-    *L = l;
+}
+
+// States that one workgroup holds in registers (up to kSmall amplitudes): the sum, the
+// addends and the result in one launch.
+constexpr int64_t kSmall = 16 * kThreads;
+
+template <typename T>
+__global__ void __launch_bounds__(kThreads) small_kernel(const T* src, T* dst, int64_t n, int64_t k, MarkedSet ms,
+                                                         double* L) {
+    constexpr int kPer = (int)(kSmall / kThreads), nw = kThreads / 64;
+    __shared__ double2 red[2][nw];
+    __shared__ double lred[nw];
+    T v[kPer];
+    unsigned marked = 0;
+    double2 s = {0.0, 0.0}, m = {0.0, 0.0};
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const int64_t e = threadIdx.x + kThreads * j;
+        v[j] = T{0, 0};
+        if (e >= n) continue;
+        v[j] = src[e];
+        for (int i = 0; i < ms.count; ++i)
+            if (e == ms.label[i]) marked |= 1u << j;
+    }
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const double2 w = wide(v[j]);
+        s.x += w.x;
+        s.y += w.y;
+        if (marked >> j & 1u) {
+            m.x += w.x;
+            m.y += w.y;
+        }
+    }
+    auto total = [&](double2 x, double2* r) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            x.x += __shfl_xor(x.x, off, 64);
+            x.y += __shfl_xor(x.y, off, 64);
+        }
+        if ((threadIdx.x & 63) == 0) r[threadIdx.x >> 6] = x;
+        __syncthreads();
+        double2 t = {0.0, 0.0};
+#pragma unroll
+        for (int w = 0; w < nw; ++w) {
+            t.x += r[w].x;
+            t.y += r[w].y;
+        }
+        return t;
+    };
+    const double2 sum = total(s, red[0]), V = total(m, red[1]);
+    const Addends r = addends(sum, V, n, ms.count, k);
+    const double sign = (k & 1) ? -1.0 : 1.0;
+    double l = 0.0;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const int64_t e = threadIdx.x + kThreads * j;
+        if (e >= n) continue;
+        const bool hit = marked >> j & 1u;
+        const T w = hit ? plus(v[j], 1.0, r.b) : plus(v[j], sign, r.a);
+        dst[e] = w;
+        const double2 c = wide(w);
+        if (hit) l += c.x * c.x + c.y * c.y;
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off, 64);
+    if ((threadIdx.x & 63) == 0) lred[threadIdx.x >> 6] = l;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double t = 0.0;
+        for (int w = 0; w < nw; ++w) t += lred[w];
+        *L = t;
+    }
 }
 
 template <typename T>
 hipError_t search_t(const void* psi_in, void* psi_out, int64_t n, const MarkedSet& ms, int64_t iters,
-                    double2* part, double2* mean, double* L, hipStream_t st) {
-    const int64_t chunk = (n + kGrid - 1) / kGrid;
-    const int grid = (int)((n + chunk - 1) / chunk);
+                    double2* part, double2* add, double* L, hipStream_t st) {
     const T* in = static_cast<const T*>(psi_in);
     T* out = static_cast<T*>(psi_out);
-    hipLaunchKernelGGL(sum_kernel<T>, dim3(grid), dim3(kThreads), 0, st, in, n, chunk, part);
-    hipLaunchKernelGGL(combine_kernel<T>, dim3(1), dim3(64), 0, st, part, grid, ms, const_cast<T*>(in), n, mean, L,
-                       0);
-    for (int64_t k = 0; k < iters; ++k) {
-        hipLaunchKernelGGL(diffuse_kernel<T>, dim3(grid), dim3(kThreads), 0, st, k == 0 ? in : out, out, n, chunk,
-                           mean, part);
-        hipLaunchKernelGGL(combine_kernel<T>, dim3(1), dim3(64), 0, st, part, grid, ms, out, n, mean, L, 1);
+    if (n <= kSmall) {
+        hipLaunchKernelGGL(small_kernel<T>, dim3(1), dim3(kThreads), 0, st, in, out, n, iters, ms, L);
+        return hipGetLastError();
     }
+    // at least four amplitudes a thread, at most kGrid blocks
+    int64_t chunk = (n + kGrid - 1) / kGrid;
+    if (chunk < 4 * kThreads) chunk = 4 * kThreads;
+    const int grid = (int)((n + chunk - 1) / chunk);
+    hipLaunchKernelGGL(sum_kernel<T>, dim3(grid), dim3(kThreads), 0, st, in, n, chunk, part);
+    hipLaunchKernelGGL(combine_kernel<T>, dim3(1), dim3(64), 0, st, part, grid, ms, in, n, iters, add, L);
+    hipLaunchKernelGGL(apply_kernel<T>, dim3(grid), dim3(kThreads), 0, st, in, out, n, chunk,
+                       (iters & 1) ? -1.0 : 1.0, add, ms);
     return hipGetLastError();
 }
 
@@ -159,10 +275,10 @@ size_t search_workspace_bytes() { return (size_t)(kGrid + 2) * sizeof(double2); 
 hipError_t launch_search(const void* psi_in, void* psi_out, int nq, bool fp64, const MarkedSet& ms, int64_t iters,
                          void* workspace, double* L, hipStream_t st) {
     double2* part = static_cast<double2*>(workspace);
-    double2* mean = part + kGrid;
+    double2* add = part + kGrid;
     const int64_t n = (int64_t)1 << nq;
-    return fp64 ? search_t<double2>(psi_in, psi_out, n, ms, iters, part, mean, L, st)
-                : search_t<float2>(psi_in, psi_out, n, ms, iters, part, mean, L, st);
+    return fp64 ? search_t<double2>(psi_in, psi_out, n, ms, iters, part, add, L, st)
+                : search_t<float2>(psi_in, psi_out, n, ms, iters, part, add, L, st);
 }
 
 }  // namespace pk

@@ -1,0 +1,58 @@
+"""Edges of the kernels' dispatch rules (GPU): the sizes and options where a launch
+changes its form, each against a plain computation of the same quantity.
+"""
+
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from paper_0902_0699_amd import workload as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _pk():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_0902_0699_amd import paperkern
+    return paperkern
+
+
+def _state(nq, seed):
+    rng = np.random.default_rng(seed)
+    v = rng.standard_normal(1 << nq) + 1j * rng.standard_normal(1 << nq)
+    return v / np.linalg.norm(v)
+
+
+# One workgroup holds up to 2^12 amplitudes; above, chunks of at least 1024 in at most
+# 2048 blocks (2^21: the first size with more than 1024 a chunk... 2^22 the next).
+@pytest.mark.parametrize("nq,marks,k", [(1, 1, 1), (1, 2, 3), (3, 8, 4), (6, 0, 5), (6, 64, 7), (11, 1, 35), (12, 1, 50),
+                                        (12, 64, 2), (13, 1, 71), (13, 64, 9), (14, 0, 3), (21, 3, 6), (22, 5, 3)])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_diffusion_addends_at_the_size_limits(nq, marks, k, prec):
+    """k iterations from a random state against k applications of 2 mean(O C) - O C.
+    The loop rounds each amplitude about four times an iteration (FP64, u = 2^-53) and
+    the kernel a bounded number of times, to single precision once at the end: the
+    normwise difference is at most (4 k + 40) u, plus 2 u32 for FP32."""
+    pk = _pk()
+    dt = torch.complex128 if prec == "fp64" else torch.complex64
+    x = torch.from_numpy(_state(nq, 31 * nq + marks)).to(dt)
+    rng = np.random.default_rng(5)
+    marked = sorted(int(v) for v in rng.choice(1 << nq, marks, replace=False))
+    want = x.to(torch.complex128).numpy().copy()
+    for _ in range(k):
+        want[marked] *= -1
+        want = 2.0 * want.mean() - want
+    print("diffusion n_q=%d marks=%d k=%d %s" % (nq, marks, k, prec), flush=True)
+    dev = x.to("cuda")
+    out, L = pk.search_diffusion(nq, marked, k, dev)
+    tol = (4 * k + 40) * 2.0 ** -53 + (2 * 2.0 ** -24 if prec == "fp32" else 0.0)
+    got = out.cpu().to(torch.complex128).numpy()
+    assert np.linalg.norm(got - want) <= tol * np.linalg.norm(want)
+    wl = float(np.sum(np.abs(want[marked]) ** 2))
+    assert abs(L.item() - wl) <= 4 * tol
+    pk.search_diffusion(nq, marked, k, dev, out=dev)  # in place
+    assert torch.equal(dev, out)
