@@ -108,7 +108,6 @@ hipError_t launch_marginal(int nq, int n_low, bool fp64, bool bitrev, const void
 // The ensemble density matrix (pk_density.hip): rho = sum_a P_a C_a C_a^H for A
 // universe states of N amplitudes (rows of C), and the entropy / purity sums of
 // a spectrum.
-int64_t density_blocks(int64_t N);
 hipError_t launch_density(const void* C, const double* P, void* rho, int64_t N, int A, hipStream_t st);
 hipError_t launch_spectrum_sums(const double* lam, int64_t n, double* out, hipStream_t st);
 // The noise-free Grover search by the diffusion identity (pk_search.hip).

@@ -56,3 +56,22 @@ def test_diffusion_addends_at_the_size_limits(nq, marks, k, prec):
     assert abs(L.item() - wl) <= 4 * tol
     pk.search_diffusion(nq, marked, k, dev, out=dev)  # in place
     assert torch.equal(dev, out)
+
+
+# The block sizes change at N = 512, 2048 and 4096, the waves at A = 1024; A = 1 leaves
+# all waves but one idle, 5 one full MFMA group and a remainder.
+@pytest.mark.parametrize("nq,A", [(1, 1), (3, 5), (4, 1025), (8, 1024), (8, 1025), (9, 5), (9, 63), (10, 1), (11, 3),
+                                  (11, 66), (12, 9)])
+def test_density_at_the_block_size_limits(nq, A):
+    """Every element against numpy: A products of two complex numbers with a weight,
+    4 A + 4 roundings of terms at most P_a |C_n| |C_n'|."""
+    pk = _pk()
+    rng = np.random.default_rng(100 * nq + A)
+    s = rng.standard_normal((A, 1 << nq)) + 1j * rng.standard_normal((A, 1 << nq))
+    w = rng.random(A) + 0.1
+    print("density n_q=%d universes=%d" % (nq, A), flush=True)
+    rho = pk.density_matrix(torch.from_numpy(s).to("cuda"), torch.from_numpy(w).to("cuda")).cpu().numpy()
+    want = (s * w[:, None]).T @ s.conj()
+    terms = (np.abs(s) * w[:, None]).T @ np.abs(s)
+    assert np.all(np.abs(rho - want) <= (8 * A + 8) * 2.0 ** -53 * terms)
+    assert np.array_equal(rho, rho.conj().T)
