@@ -506,6 +506,13 @@ hipError_t enqueue_backward(DevPlan* d, const BwdArgs& a, hipStream_t st) {
     const Instance& in = P.inst[0];
     for (size_t p = 0; p < in.bwd.size(); ++p) {
         set_pass(&L, P, in.bwd[p], P.n_fwd_passes + (int)p);
+        if (in.bwd[p].flags & PASS_LAMBDA) {
+            // lambda is the pass's only vector, in place in grad_psi (a first pass takes
+            // its seeds from psi_out)
+            L.nv = 1;
+            L.src0 = p == 0 ? a.psi_out : a.grad_psi;
+            L.dst0 = a.grad_psi;
+        }
         e = launch_pass(L, st);
         if (e != hipSuccess) return e;
     }

@@ -117,7 +117,7 @@ enum HeadWord {
     HD_FLIP_MID = 10,
     HD_READ = 12,      // tile, local label, readout slot
     HD_MAT4 = 15, HD_MAT4B = 16,
-    HD_SEED = 20,      // tile, local label, instance
+    HD_SEED = 20,      // tile, local label, instance, state label
     HD_WORDS = 24,
 };
 
@@ -184,6 +184,7 @@ struct Flip {
     int64_t tile;
     int32_t j;
     int32_t slot; // READ: readout slot; SEED: instance index
+    int64_t label; // state label of the amplitude
 };
 
 enum PassFlags : int32_t {
@@ -191,11 +192,12 @@ enum PassFlags : int32_t {
     PASS_LAST = 2,     // final pass of the instance
     PASS_NORM = 4,     // (reserved)
     PASS_SKIP_V0 = 8,  // do not store vector 0 (backward: the recovered psi_in is not needed)
-    PASS_SEED_V1 = 16, // vector 1 is not read: it starts as zero and is seeded (backward start)
+    PASS_SEED_V1 = 16, // lambda is not read: it starts as zero and is seeded (backward start)
     PASS_WIDE = 32,    // a thread's byte offset inside a tile may exceed 32 bits
     PASS_STREAM = 64,  // loads and stores are nontemporal (streaming): the last forward pass of
                        // an FP64 instance far larger than the memory-side cache, when it
                        // writes the tile back in the layout it read
+    PASS_LAMBDA = 128, // backward: lambda alone (a one-vector pass), psi is not needed any more
 };
 
 // State size from which an FP64 instance's last forward pass streams

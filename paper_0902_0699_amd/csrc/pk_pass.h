@@ -586,13 +586,14 @@ template <typename R, int NV, int NR, bool NT = false>
 __device__ __forceinline__ void load_tile(const KArgs& a, const PassCtx& C, int64_t base,
                                           typename Cplx<R>::T (&v)[NV][NR]) {
     using T = typename Cplx<R>::T;
-    if (C.nreg < NR || NV == 2) {
+    const bool unread = NV == 1 && (C.flags & PASS_SEED_V1);  // lambda alone, not yet seeded
+    if (C.nreg < NR || NV == 2 || unread) {
 #pragma unroll
         for (int n = 0; n < NV; ++n)
 #pragma unroll
             for (int i = 0; i < NR; ++i) v[n][i] = T{0, 0};
     }
-    if (!C.active) return;
+    if (!C.active || unread) return;
     const char* in0 = reinterpret_cast<const char*>((C.flags & PASS_FIRST) ? a.src0 : a.dst0);
     const char* in1 = reinterpret_cast<const char*>(a.dst1);
     const bool read1 = NV == 2 && !(C.flags & PASS_SEED_V1);
@@ -695,10 +696,12 @@ __device__ __forceinline__ void element_op(const KArgs& a, T (&v)[NV][NR], const
                 const double x = v[0][i].x, y = v[0][i].y;
                 publish(a, a.reads + slot, x * x + y * y);
             }
-        } else if constexpr (NV == 2) {
+        } else {
+            // lambda is the last vector; without psi beside it, psi's amplitude is read
             const auto d = (decltype(v[0][0].x))a.dL[slot];
-            v[1][i].x = hit ? d * v[0][i].x : v[1][i].x;
-            v[1][i].y = hit ? d * v[0][i].y : v[1][i].y;
+            const T x = NV == 2 ? v[0][i] : reinterpret_cast<const T*>(a.src0)[(unsigned)el[3]];
+            v[NV - 1][i].x = hit ? d * x.x : v[NV - 1][i].x;
+            v[NV - 1][i].y = hit ? d * x.y : v[NV - 1][i].y;
         }
     }
 }
@@ -710,7 +713,7 @@ __device__ __forceinline__ T& lds_at(T* lds, unsigned off) {
 }
 
 // Every stage of the pass on one tile held in registers, then the norm partial.
-template <typename R, int NV, int KMAX, int RB>
+template <typename R, int NV, int KMAX, int RB, bool FULL>
 __device__ __forceinline__ void compute_tile(const KArgs& a, const PK_CONST Pass* P, const PassCtx& C,
                                              int64_t tile, typename Cplx<R>::T (&v)[NV][1 << RB],
                                              const TileRefs<R>& U, typename Cplx<R>::T* lds, double* red) {
@@ -749,7 +752,7 @@ __device__ __forceinline__ void compute_tile(const KArgs& a, const PK_CONST Pass
             L = Ln;
         }
         // ---- the sub-stage's steps, in their fixed order
-        if constexpr (NV == 2) {
+        if constexpr (NV == 2 || !FULL) {
             if (steps & ST_SEED) element_op<NV, NR, 2>(a, v, L, S->head + HD_SEED, tile, nreg, active);
         }
         if (steps & ST_FLIP_PRE) element_op<NV, NR, 0>(a, v, L, S->head + HD_FLIP_PRE, tile, nreg, active);
@@ -866,7 +869,7 @@ __device__ __forceinline__ void run_tiles_ph(const KArgs& a, const PK_CONST Pass
     if constexpr (FULL) {
         C.active = true;
         C.nreg = NR;
-        C.flags &= ~PASS_WIDE;
+        C.flags &= ~(PASS_WIDE | PASS_SEED_V1);
     }
     const int64_t off = P->state_off;
     // the runs of the tile index: the first four stay in scalar registers
@@ -904,7 +907,7 @@ __device__ __forceinline__ void run_tiles_ph(const KArgs& a, const PK_CONST Pass
             const int64_t base = base_of(tile);
             const TileRefs<R> u = refs_of(tile);
             load_tile<R, NV, NR, NT>(a, C, base, v);
-            compute_tile<R, NV, KMAX, RB>(a, P, C, tile, v, u, lds, red);
+            compute_tile<R, NV, KMAX, RB, FULL>(a, P, C, tile, v, u, lds, red);
             store_tile<R, NV, NR, NT>(a, C, base, v);
         }
     } else {
@@ -920,7 +923,7 @@ __device__ __forceinline__ void run_tiles_ph(const KArgs& a, const PK_CONST Pass
             const int64_t baseb = base_of(tbc);
             const TileRefs<R> ub = refs_of(tbc);
             if (FULL || tb < ntiles) load_tile<R, 1, NR, NT>(a, C, baseb, vb);
-            compute_tile<R, 1, KMAX, RB>(a, P, C, ta, va, ua, lds, red);
+            compute_tile<R, 1, KMAX, RB, FULL>(a, P, C, ta, va, ua, lds, red);
             store_tile<R, 1, NR, NT>(a, C, basea, va);
             if (tb >= ntiles) break;
             int64_t jc = jb;
@@ -929,7 +932,7 @@ __device__ __forceinline__ void run_tiles_ph(const KArgs& a, const PK_CONST Pass
             const int64_t basec = base_of(tcc);
             ua = refs_of(tcc);
             if (FULL || tc < ntiles) load_tile<R, 1, NR, NT>(a, C, basec, va);
-            compute_tile<R, 1, KMAX, RB>(a, P, C, tb, vb, ub, lds, red);
+            compute_tile<R, 1, KMAX, RB, FULL>(a, P, C, tb, vb, ub, lds, red);
             store_tile<R, 1, NR, NT>(a, C, baseb, vb);
             if (tc >= ntiles) break;
             ta = tc;

@@ -359,6 +359,7 @@ void pack_head(Stage& s, const std::vector<Flip>& flips) {
     flip(HD_FLIP_MID, s.flip_mid, false);
     flip(HD_READ, s.read, true);
     flip(HD_SEED, s.seed, true);
+    if (s.seed >= 0) s.head[HD_SEED + 3] = (int32_t)flips[s.seed].label;
     s.head[HD_MAT4] = s.mat4;
     s.head[HD_MAT4B] = s.mat4b;
 }
@@ -544,6 +545,7 @@ struct Compiler {
         f.j = (int32_t)extract(x, tbits);
         f.tile = extract(x, free_bits(tbits));
         f.slot = slot;
+        f.label = x;
         plan->flips.push_back(f);
         return (int)plan->flips.size() - 1;
     }
@@ -893,6 +895,19 @@ struct Compiler {
         return passes;
     }
 
+    // psi is walked back only for the rotations' angle gradients: the pass with the last
+    // of them stores lambda alone, and the passes after it carry lambda alone (half the
+    // traffic, and the one-vector kernel's prefetch).  Without rotations every pass does.
+    static void lambda_only(std::vector<HostPass>* passes) {
+        int last = -1;
+        for (size_t p = 0; p < passes->size(); ++p)
+            for (const HostStage& hs : (*passes)[p].stages)
+                for (const Op& o : hs.ops)
+                    if (o.kind == OP_D2BWD || o.kind == OP_D4BWD) last = (int)p;
+        if (last >= 0) (*passes)[last].flags |= PASS_SKIP_V0;
+        for (size_t p = last + 1; p < passes->size(); ++p) (*passes)[p].flags |= PASS_LAMBDA;
+    }
+
     void compile(const std::vector<Prim>& prims, std::vector<HostPass>* out) {
         const int nq = in->nq;
         const int n = (int)prims.size();
@@ -954,7 +969,7 @@ struct Compiler {
             hp.rbits = RBITS;
             hp.kmax = std::max(k, RBITS + kWaveBits);
             if (pass_no == 0) hp.flags |= PASS_FIRST | (backward ? PASS_SEED_V1 : 0);
-            if (last) hp.flags |= PASS_LAST | (backward ? PASS_SKIP_V0 : 0);
+            if (last) hp.flags |= PASS_LAST;
             for (size_t s = 0; s < st.size(); ++s) {
                 HostStage hs;
                 for (int a = 0; a < kMaxRegBits; ++a) hs.rb[a] = a < (int)st[s].first.size() ? st[s].first[a] : -1;
@@ -1094,6 +1109,7 @@ struct Compiler {
             out->push_back(hp);
             ++pass_no;
         } while (left > 0);
+        if (backward) lambda_only(out);
     }
 };
 

@@ -75,3 +75,61 @@ def test_density_at_the_block_size_limits(nq, A):
     terms = (np.abs(s) * w[:, None]).T @ np.abs(s)
     assert np.all(np.abs(rho - want) <= (8 * A + 8) * 2.0 ** -53 * terms)
     assert np.array_equal(rho, rho.conj().T)
+
+
+# Without rotations every backward pass carries lambda alone, seeded from psi_out in the
+# first; with rotations the passes after the last of them do.  Sizes of one, three and
+# (tile 2^6) many passes.
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("nq,tile,rotations,marks", [(5, None, 0, 3), (13, None, 0, 64), (15, None, 0, 1),
+                                                     (15, None, 1, 2), (14, 6, 0, 8), (14, 6, 2, 8)])
+def test_backward_with_lambda_alone(nq, tile, rotations, marks, prec):
+    """grad psi_in and the angle gradients against the oracle's adjoint: FP64 to its
+    1e-10 bar; FP32 to 1e-5 (the precision's bar on a state) of the gradient's norm."""
+    pk = _pk()
+    rng = np.random.default_rng(nq * 10 + rotations)
+    marked = sorted(int(v) for v in rng.choice(1 << nq, marks, replace=False))
+    gates = [("ORACLE",), ("HALL",)]
+    gates += [("D2", 1 + int(rng.integers(nq)), 0.3 + r, 1.1, -0.4) for r in range(rotations)]
+    gates += [("INV",), ("HALL",), ("CPHASEK", 1, nq, 3), ("SWAP", 2, 3), ("H", 2)]
+    psi = _state(nq, nq)
+    dt = torch.complex128 if prec == "fp64" else torch.complex64
+    plan = pk.Plan({"nq": nq, "gates": gates, "marked": marked}, prec=prec)
+    if tile:
+        plan.set_tiling(tile, 3)
+    print("backward n_q=%d tile %s rotations %d %s" % (nq, tile, rotations, prec), flush=True)
+    out, _, _ = pk.evaluate(plan, torch.from_numpy(psi).to(dt).to("cuda"))
+    gpsi, gang = pk.backward(plan, out, torch.tensor([0.75], dtype=torch.float64, device="cuda"))
+    wpsi, wang = O.adjoint_grad(nq, gates, marked, psi, 0.75)
+    tol = 1e-10 if prec == "fp64" else 1e-5
+    got = gpsi.cpu().to(torch.complex128).numpy()
+    assert np.linalg.norm(got - wpsi) <= tol * np.linalg.norm(wpsi)
+    if rotations:
+        # an angle's gradient is at most the two states' norms: ||lambda|| ||psi||
+        scale = np.linalg.norm(wpsi)
+        assert np.max(np.abs(gang.cpu().numpy() - np.asarray(wang).reshape(-1))) <= tol * scale
+
+
+# The last pass combines L and the norm itself up to 2^12 tiles (one workgroup, some, all
+# resident at once or not), a launch of its own above.
+@pytest.mark.parametrize("nq,tile,marks", [(1, None, 2), (8, 4, 1), (16, 4, 64), (17, 4, 64), (18, 12, 5)])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_readouts_at_the_combine_limit(nq, tile, marks, prec):
+    """L and the norm against sums over the returned amplitudes, three calls in a row (the
+    ticket starts each at zero): FP64 sums of n terms, each rounded twice, in any order
+    differ by at most n 2^-52 relative; FP32 squares by 2^-22 relative besides."""
+    pk = _pk()
+    rng = np.random.default_rng(nq)
+    marked = sorted(int(v) for v in rng.choice(1 << nq, marks, replace=False))
+    dt = torch.complex128 if prec == "fp64" else torch.complex64
+    plan = pk.Plan({"nq": nq, "gates": W.grover_gates((1, 1, 0.4, 0.9, 0.0)), "marked": marked}, prec=prec)
+    if tile:
+        plan.set_tiling(tile, 3)
+    print("readouts n_q=%d tile %s %s" % (nq, tile, prec), flush=True)
+    x = torch.from_numpy(_state(nq, 3)).to(dt).to("cuda")
+    for _ in range(3):
+        out, L, norm = pk.evaluate(plan, x)
+        p = np.abs(out.cpu().to(torch.complex128).numpy()) ** 2
+        tol = (1 << nq) * 2.0 ** -52 + (2.0 ** -22 if prec == "fp32" else 0.0)
+        assert abs(L.item() - math.fsum(p[marked])) <= tol * math.fsum(p[marked])
+        assert abs(norm.item() - math.fsum(p)) <= tol * math.fsum(p)
