@@ -137,8 +137,11 @@ int pk_create(const pk_problem* probs, int32_t n_inst, int32_t prec, pk_plan** o
  * 0 for FP32) -- a tile whose amplitudes span many 2 MiB pages misses the
  * per-CU address translation cache on most loads, so these bits are best spread
  * over the passes.  Re-compiles the schedule and drops captured graphs.
- * Defaults: 2^13-amplitude tiles (FP64 and FP32), 4 carriers, fusion on,
- * lane_order 1, page_cap -1.  PK_EINVAL when out of range (page_cap -1..16).
+ * Defaults: 4 carriers, fusion on, lane_order 1, page_cap -1, and tiles of 2^13
+ * amplitudes for a batch.  For a single instance the library picks tile and register
+ * bits from its size and gates (tiles of 2^10 to 2^13) until pk_set_tiling or
+ * pk_set_launch is called; the one that was not called then stands at 2^13
+ * amplitudes or the register bits of pk_set_launch's 0.  PK_EINVAL when out of range (page_cap -1..16).
  */
 int pk_set_tiling(pk_plan* plan, int32_t tile_bits, int32_t carrier_bits, int32_t fuse, int32_t lane_order,
                   int32_t page_cap);
@@ -148,9 +151,10 @@ int pk_set_tiling(pk_plan* plan, int32_t tile_bits, int32_t carrier_bits, int32_
  * workgroups per CU (1..8, or 0 for as many as the kernel's resources allow,
  * the default; more than fit only queue up), and reg_bits = 3, 4 or 5 register
  * bits per thread in forward passes (8, 16 or 32 amplitudes per thread, a
- * workgroup of 2^(tile_bits - reg_bits) threads, at most 1024; 0 selects the
- * default: 4 for FP64, 5 for FP32).  With 3, a stage holds one two-qubit pair
- * and pk_evaluate_batched returns PK_EUNSUPPORTED.  Backward passes always use
+ * workgroup of 2^(tile_bits - reg_bits) threads, at most 1024; 0 selects 4 for
+ * FP64, 5 for FP32).  With 3 set here, a stage holds one two-qubit pair and
+ * pk_evaluate_batched returns PK_EUNSUPPORTED.  (A single-instance plan on which
+ * neither this nor pk_set_tiling was called: see there.)  Backward passes always use
  * 4.  Changing reg_bits re-compiles the schedule.  Drops captured graphs.
  * PK_EINVAL when out of range.
  */
@@ -160,8 +164,9 @@ int pk_set_launch(pk_plan* plan, int32_t wgs_per_cu, int32_t reg_bits);
  * pk_set_pass_walk -- the order in which a single-instance plan's passes hand
  * tiles to workgroups: one entry per forward pass (n = pk_plan_passes), or one
  * per forward pass followed by one per backward pass (pk_backward); n = 0
- * resets every pass to 0.  Over a grid of G workgroups,
- * workgroup w takes: 0, tiles w, w + G, ... (the default: the workgroups
+ * leaves the choice to the library (by precision and tile count; 0 in most
+ * passes), as before the first call.  Over a grid of G workgroups,
+ * workgroup w takes: 0, tiles w, w + G, ... (the workgroups
  * resident at once cover neighbouring tiles); c in 2..65536, runs of c
  * consecutive tiles starting at tiles w c, (w + G) c, ...; -1, one contiguous
  * block of ceil(ntiles / G) tiles.  Results do not change; which walk is faster
@@ -174,11 +179,12 @@ int pk_set_pass_walk(pk_plan* plan, int32_t n, const int32_t* walk);
 
 /*
  * pk_set_pass_overlap -- how a single-instance plan's forward passes pipeline
- * HBM and LDS: one entry per forward pass (n = pk_plan_passes) or n = 0 to reset
- * every pass to 0.  1: the pass keeps the next tile's loads in flight through
+ * HBM and LDS: one entry per forward pass (n = pk_plan_passes) or n = 0 to leave
+ * the choice to the library (by tile count, precision and gates), as before the first
+ * call.  1: the pass keeps the next tile's loads in flight through
  * all of the current tile's LDS exchanges (the tile loop that issues the same
  * loads on every path, so that only the current tile's loads are waited for);
- * 0: they are waited for at the first exchange.  It applies to the FP64 kernels
+ * 0: they are waited for at the first exchange.  It applies to the kernels
  * with 4 register bits and to passes whose tiles fill the workgroup; elsewhere
  * it is accepted and changes nothing.  Results do not change; which setting is
  * faster depends on the pass and is measured
@@ -298,7 +304,7 @@ int pk_evaluate_static(pk_plan* plan, const void* psi_in, void* psi_out, double*
  * alone, first.  The whole sequence of passes, one launch each, is captured into
  * one hipGraph, keyed by the pointers and reps, and replayed.  With the environment
  * variable PK_REPEAT_PERSISTENT=1 (and reps > 1, every pass on one kernel
- * instance) the passes run instead in one persistent launch of as many
+ * instance with 4 or 5 register bits) the passes run instead in one persistent launch of as many
  * workgroups as the GPU holds at once, with a grid-wide barrier between passes;
  * same results bit for bit, but on MI355X the barrier's device-scope fences cost
  * more than the kernel boundaries.  If its workgroups cannot all be resident (the
@@ -347,7 +353,8 @@ int pk_search_workspace_bytes(int64_t* bytes);
 
 /*
  * pk_evaluate_batched -- evaluate every instance of the plan ("multiverses",
- * Sec. 6.2) in one persistent launch (after one that clears its queue).  States are
+ * Sec. 6.2) in one persistent launch (after one that clears its queue); a single
+ * instance whose tiling is the library's choice runs as pk_evaluate does.  States are
  * packed at pk_plan_offsets(); L_out and norm_out (or NULL) hold n_inst doubles.
  * Other arguments as pk_evaluate.
  */

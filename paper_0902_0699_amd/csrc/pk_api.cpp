@@ -668,13 +668,14 @@ int pk_set_tiling(pk_plan* plan, int32_t tile_bits, int32_t carrier_bits, int32_
     if (fuse != 0 && fuse != 1) return fail(d, PK_EINVAL, "fuse must be 0 or 1");
     if (lane_order != 0 && lane_order != 1) return fail(d, PK_EINVAL, "lane_order must be 0 or 1");
     if (page_cap < -1 || page_cap > 16) return fail(d, PK_EINVAL, "page_cap must be -1..16");
-    if (tile_bits - d->host.tiling.reg_bits > 10)
+    const int rb = d->host.tiling.automatic ? default_reg_bits(d->host.prec) : d->host.tiling.reg_bits;
+    if (tile_bits - rb > 10)
         return fail(d, PK_EINVAL, "tile_bits - reg_bits must be at most 10 (1024 threads a workgroup)");
     const Tiling previous = d->host.tiling;
     d->host.walk.clear();  // the passes change with the tiling
     d->host.overlap.clear();
-    d->host.tiling = Tiling{tile_bits, carrier_bits, fuse, d->host.tiling.wgs_per_cu, d->host.tiling.reg_bits,
-                            lane_order, page_cap < 0 ? default_page_cap(d->host.prec) : page_cap};
+    d->host.tiling = Tiling{tile_bits, carrier_bits, fuse, d->host.tiling.wgs_per_cu, rb,
+                            lane_order, page_cap < 0 ? default_page_cap(d->host.prec) : page_cap, false};
     drop_device(d);
     return recompile_or_restore(d, previous);
 }
@@ -739,12 +740,15 @@ int pk_set_launch(pk_plan* plan, int32_t wgs_per_cu, int32_t reg_bits) {
     if (wgs_per_cu < 0 || wgs_per_cu > 8) return fail(d, PK_EINVAL, "wgs_per_cu must be 0..8");
     if (reg_bits != 0 && (reg_bits < 3 || reg_bits > 5)) return fail(d, PK_EINVAL, "reg_bits must be 0, 3, 4 or 5");
     const int rb = reg_bits == 0 ? default_reg_bits(d->host.prec) : reg_bits;
-    if (d->host.tiling.tile_bits - rb > 10)
+    const int tb = d->host.tiling.automatic ? default_tile_bits(d->host.prec) : d->host.tiling.tile_bits;
+    if (tb - rb > 10)
         return fail(d, PK_EINVAL, "tile_bits - reg_bits must be at most 10 (1024 threads a workgroup)");
-    const bool recompile_needed = rb != d->host.tiling.reg_bits;
+    const bool recompile_needed = rb != d->host.tiling.reg_bits || tb != d->host.tiling.tile_bits;
     const Tiling previous = d->host.tiling;
     d->host.tiling.wgs_per_cu = wgs_per_cu;
+    d->host.tiling.tile_bits = tb;
     d->host.tiling.reg_bits = rb;
+    d->host.tiling.automatic = false;
     if (recompile_needed) {
         d->host.walk.clear();  // the passes change with the register bits
         d->host.overlap.clear();
@@ -933,14 +937,18 @@ int pk_evaluate_batched(pk_plan* plan, const void* psi_in, void* psi_out, double
                         const double* angles, void* workspace, void* stream) {
     if (!valid(plan)) return fail(nullptr, PK_EINVAL, "invalid plan");
     DevPlan* d = dp(plan);
-    if (d->host.tiling.reg_bits == 3)
+    // a single instance whose settings are the library's choice runs as pk_evaluate does
+    const bool alone = d->host.inst.size() == 1 && d->host.tiling.automatic;
+    if (d->host.tiling.reg_bits == 3 && !alone)
         return fail(d, PK_EUNSUPPORTED, "the batched launch has 4 or 5 register bits (pk_set_launch)");
     int rc = check_eval_args(d, psi_in, psi_out, L_out, norm_out, angles, workspace);
     if (rc != PK_OK) return rc;
     rc = ensure_device(d);
     if (rc != PK_OK) return rc;
     EvalArgs a{psi_in, psi_out, L_out, norm_out, angles, workspace};
-    return run_direct(d, static_cast<hipStream_t>(stream), [&](hipStream_t s) { return enqueue_batched(d, a, s); });
+    return run_direct(d, static_cast<hipStream_t>(stream), [&](hipStream_t s) {
+        return alone ? enqueue_eval(d, a, s, nullptr) : enqueue_batched(d, a, s);
+    });
 }
 
 int pk_backward(pk_plan* plan, const void* psi_out, const double* dL, void* grad_psi_in, double* grad_angles,

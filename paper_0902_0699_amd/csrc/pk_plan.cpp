@@ -93,11 +93,21 @@ struct ScanItem {
     bool pair_b = true; // a two-qubit gate the second register pair (bits 2, 3) can take
 };
 
-int scan(const std::vector<ScanItem>& items, const std::vector<char>& done,
-         const std::vector<char>& in_set, int nbits, int max_gates, std::vector<int>* out,
-         int pair = PAIR_ANY, int pair2 = PAIR_NONE) {
-    std::vector<char> blocked(nbits, 0);  // later gates on the bit must wait
-    std::vector<char> nd(nbits, 0);       // later phases on the bit must wait (a non-diagonal gate is pending)
+// A set of tile or state bits (at most 31).
+using Bits = uint32_t;
+
+inline Bits bit_of(int b) { return b >= 0 ? (Bits)1 << b : 0u; }
+
+Bits bits_of(const std::vector<int>& v) {
+    Bits m = 0;
+    for (int b : v) m |= bit_of(b);
+    return m;
+}
+
+int scan(const std::vector<ScanItem>& items, const std::vector<char>& done, Bits in_set, int max_gates,
+         std::vector<int>* out, int pair = PAIR_ANY, int pair2 = PAIR_NONE) {
+    Bits blocked = 0;  // later gates on the bit must wait
+    Bits nd = 0;       // later phases on the bit must wait (a non-diagonal gate is pending)
     bool blocked_gate = false, blocked_diag = false;
     int count = 0, gates = 0;
     for (size_t i = 0; i < items.size(); ++i) {
@@ -110,34 +120,31 @@ int scan(const std::vector<ScanItem>& items, const std::vector<char>& done,
             } else {
                 blocked_diag = true;
             }
-        } else if (it.type == IT_PHASE) {
-            const bool ok = (it.bit < 0 || !nd[it.bit]) && (it.bit2 < 0 || !nd[it.bit2]) &&
-                            (max_gates < 0 || gates < max_gates);
-            if (ok) {
+            continue;
+        }
+        const Bits m = bit_of(it.bit) | bit_of(it.bit2);
+        const bool room = max_gates < 0 || gates < max_gates;
+        if (it.type == IT_PHASE) {
+            if (!(nd & m) && room) {
                 ++count;
                 ++gates;
                 if (out) out->push_back((int)i);
             } else {
-                if (it.bit >= 0) blocked[it.bit] = 1;
-                if (it.bit2 >= 0) blocked[it.bit2] = 1;
+                blocked |= m;
             }
         } else {
-            const bool two = it.bit2 >= 0;
-            bool ok = !blocked[it.bit] && !blocked_diag && in_set[it.bit] &&
-                      (max_gates < 0 || gates < max_gates);
-            if (two) {
+            bool ok = !(blocked & m) && !blocked_diag && (in_set & m) == m && room;
+            if (ok && it.bit2 >= 0) {
                 const int code = (it.bit << 8) | it.bit2;
-                const bool placed = pair == PAIR_ANY ||
-                                    (pair >= 0 && (pair == code || (pair2 >= 0 && pair2 == code && it.pair_b)));
-                ok = ok && !blocked[it.bit2] && in_set[it.bit2] && placed;
+                ok = pair == PAIR_ANY || (pair >= 0 && (pair == code || (pair2 >= 0 && pair2 == code && it.pair_b)));
             }
             if (ok) {
                 ++count;
                 ++gates;
                 if (out) out->push_back((int)i);
             } else {
-                blocked[it.bit] = nd[it.bit] = 1;
-                if (two) blocked[it.bit2] = nd[it.bit2] = 1;
+                blocked |= m;
+                nd |= m;
                 blocked_gate = true;
             }
         }
@@ -145,15 +152,57 @@ int scan(const std::vector<ScanItem>& items, const std::vector<char>& done,
     return count;
 }
 
-// Pending two-qubit gates with exactly one bit in the set: a tie-break that
-// lets a greedy bit choice complete pairs (adding one bit alone enables none).
-int half_pairs(const std::vector<ScanItem>& items, const std::vector<char>& done, const std::vector<char>& in_set) {
-    int c = 0;
+// What of the pending items a tile choice needs, without those already scheduled: the
+// choice counts ready items for thousands of bit sets.
+struct Pending {
+    Bits m;        // the item's bits
+    uint8_t type;  // ItemType
+    bool two;      // a two-qubit gate
+};
+
+std::vector<Pending> pending_of(const std::vector<ScanItem>& items, const std::vector<char>& done) {
+    std::vector<Pending> p;
+    p.reserve(items.size());
     for (size_t i = 0; i < items.size(); ++i)
-        if (!done[i] && items[i].type == IT_GATE && items[i].bit2 >= 0 &&
-            (in_set[items[i].bit] != in_set[items[i].bit2]))
-            ++c;
-    return c;
+        if (!done[i])
+            p.push_back({bit_of(items[i].bit) | bit_of(items[i].bit2), (uint8_t)items[i].type,
+                         items[i].type == IT_GATE && items[i].bit2 >= 0});
+    return p;
+}
+
+// Twice the items that scan() finds ready for a tile with the bits `in_set` (any
+// pairs), plus the pending two-qubit gates with exactly one bit in it: a tie-break that
+// lets a greedy bit choice complete pairs (adding one bit alone enables none).
+int tile_gain(const std::vector<Pending>& pend, Bits in_set, int max_gates) {
+    Bits blocked = 0, nd = 0;
+    bool blocked_gate = false, blocked_diag = false;
+    int gain = 0, gates = 0;
+    for (const Pending& it : pend) {
+        const bool room = max_gates < 0 || gates < max_gates;
+        if (it.type == IT_GATE) {
+            if (it.two && (in_set & it.m) != 0 && (in_set & it.m) != it.m) ++gain;
+            if (!(blocked & it.m) && !blocked_diag && (in_set & it.m) == it.m && room) {
+                gain += 2;
+                ++gates;
+            } else {
+                blocked |= it.m;
+                nd |= it.m;
+                blocked_gate = true;
+            }
+        } else if (it.type == IT_PHASE) {
+            if (!(nd & it.m) && room) {
+                gain += 2;
+                ++gates;
+            } else {
+                blocked |= it.m;
+            }
+        } else if (!blocked_gate) {
+            gain += 2;
+        } else {
+            blocked_diag = true;
+        }
+    }
+    return gain;
 }
 
 struct ScaleState {
@@ -636,10 +685,7 @@ struct Compiler {
                         for (int b = 0; b < k; ++b) {
                             if (std::find(r.begin(), r.end(), b) != r.end()) continue;
                             if (first && !io_ok(b)) continue;
-                            std::vector<char> in_set(k, 0);
-                            for (int x : r) in_set[x] = 1;
-                            in_set[b] = 1;
-                            int g = scan(items, done, in_set, k, -1, nullptr, opt.first, opt.second);
+                            int g = scan(items, done, bits_of(r) | bit_of(b), -1, nullptr, opt.first, opt.second);
                             // first stage: prefer high bits; later: bits that cannot be
                             // stored from (low carriers) first, then low bits
                             int pref = first ? b : ((!io_ok(b) ? 1000 : 0) + (k - b));
@@ -652,9 +698,7 @@ struct Compiler {
                         if (best < 0) break;
                         r.push_back(best);
                     }
-                    std::vector<char> in_set(k, 0);
-                    for (int x : r) in_set[x] = 1;
-                    const int g = scan(items, done, in_set, k, -1, nullptr, opt.first, opt.second);
+                    const int g = scan(items, done, bits_of(r), -1, nullptr, opt.first, opt.second);
                     if (g > best_gain) {
                         best_gain = g;
                         rb = r;
@@ -663,10 +707,8 @@ struct Compiler {
                     }
                 }
             }
-            std::vector<char> in_set(k, 0);
-            for (int r : rb) in_set[r] = 1;
             std::vector<int> sel;
-            scan(items, done, in_set, k, -1, &sel, pair, pair2);
+            scan(items, done, bits_of(rb), -1, &sel, pair, pair2);
             for (int i : sel) done[i] = 1;
             left -= (int)sel.size();
             stages.push_back({rb, sel});
@@ -691,18 +733,24 @@ struct Compiler {
                                  std::vector<int>* sel) const {
         const int nq = in->nq;
         const int max_gates = plan->tiling.fuse ? -1 : 1;
-        std::vector<char> in_t(nq, 0);
+        Bits in_t = 0;
         std::vector<int> t;
-        for (int b = 0; b < C; ++b) {
-            in_t[b] = 1;
+        auto take = [&](int b) {
+            in_t |= bit_of(b);
             t.push_back(b);
-        }
+        };
+        for (int b = 0; b < C; ++b) take(b);
+        const std::vector<Pending> pend = pending_of(items, done);
+        Bits useful = 0;
+        for (const Pending& it : pend)
+            if (it.type == IT_GATE) useful |= it.m;
         // Among bits of equal gain, take bits at byte strides of 2 MiB or more (each
         // doubles the pages a tile touches) first while the tile has fewer than
         // page_cap of them, so that no later pass is left with all of them.
         const int pbit = kPageByteBit - (plan->prec == PK_FP64 ? 4 : 3);
         while ((int)t.size() < k) {
             int best = -1, best_gain = -1;
+            const int base = tile_gain(pend, in_t, max_gates);
             int npage = 0;
             for (int b : t) npage += b >= pbit;
             std::vector<int> cand;
@@ -711,21 +759,19 @@ struct Compiler {
             for (int b = 0; b < nq; ++b)
                 if (!(pcap > 0 && npage < pcap && b >= pbit)) cand.push_back(b);
             for (int b : cand) {
-                if (in_t[b]) continue;
-                in_t[b] = 1;
-                int g = 2 * scan(items, done, in_t, nq, max_gates, nullptr) + half_pairs(items, done, in_t);
-                in_t[b] = 0;
+                if (in_t & bit_of(b)) continue;
+                // a bit of no pending gate leaves the gain as it is
+                const int g = (useful & bit_of(b)) ? tile_gain(pend, in_t | bit_of(b), max_gates) : base;
                 if (g > best_gain) {
                     best = b;
                     best_gain = g;
                 }
             }
-            in_t[best] = 1;
-            t.push_back(best);
+            take(best);
         }
         std::sort(t.begin(), t.end());
         sel->clear();
-        scan(items, done, in_t, nq, max_gates, sel);
+        scan(items, done, in_t, max_gates, sel);
         if (sel->empty()) {
             // the greedy choice enables nothing (the half-pair tie-break can lead it
             // away from the first pending two-qubit gate): build the tile around the
@@ -733,25 +779,16 @@ struct Compiler {
             int first = -1;
             for (size_t i = 0; i < items.size() && first < 0; ++i)
                 if (!done[i] && items[i].type == IT_GATE) first = (int)i;
-            std::fill(in_t.begin(), in_t.end(), 0);
+            in_t = 0;
             t.clear();
-            for (int b = 0; b < C; ++b) {
-                in_t[b] = 1;
-                t.push_back(b);
-            }
+            for (int b = 0; b < C; ++b) take(b);
             if (first >= 0)
                 for (int b : {items[first].bit, items[first].bit2})
-                    if (b >= 0 && !in_t[b]) {
-                        in_t[b] = 1;
-                        t.push_back(b);
-                    }
+                    if (b >= 0 && !(in_t & bit_of(b))) take(b);
             for (int b = 0; b < nq && (int)t.size() < k; ++b)
-                if (!in_t[b]) {
-                    in_t[b] = 1;
-                    t.push_back(b);
-                }
+                if (!(in_t & bit_of(b))) take(b);
             std::sort(t.begin(), t.end());
-            scan(items, done, in_t, nq, max_gates, sel);
+            scan(items, done, in_t, max_gates, sel);
         }
         return t;
     }
@@ -826,8 +863,7 @@ struct Compiler {
             auto rest = greedy_rest(items, d, left - (int)s.size());
             return std::pair<int, int>{1 + rest.first, ns * ns + rest.second};
         };
-        std::vector<char> in_t(nq, 0);
-        for (int b : t) in_t[b] = 1;
+        Bits in_t = bits_of(t);
         std::vector<int> best = sel;
         auto best_cost = cost_of(sel);
         for (;;) {
@@ -835,15 +871,13 @@ struct Compiler {
             auto round_cost = best_cost;
             int drop = -1;
             for (int b : t) {
-                if (!in_t[b]) continue;
+                if (!(in_t & bit_of(b))) continue;
                 bool used = false;
                 for (int i : best)
                     used = used || (items[i].type == IT_GATE && (items[i].bit == b || items[i].bit2 == b));
                 if (!used) continue;
-                in_t[b] = 0;
                 std::vector<int> s;
-                scan(items, done, in_t, nq, -1, &s);
-                in_t[b] = 1;
+                scan(items, done, in_t & ~bit_of(b), -1, &s);
                 if (s.empty()) continue;
                 auto c = cost_of(s);
                 if (c < round_cost) {
@@ -853,7 +887,7 @@ struct Compiler {
                 }
             }
             if (drop < 0) break;
-            in_t[drop] = 0;
+            in_t &= ~bit_of(drop);
             best = round_best;
             best_cost = round_cost;
         }
@@ -908,8 +942,7 @@ struct Compiler {
         for (size_t p = last + 1; p < passes->size(); ++p) (*passes)[p].flags |= PASS_LAMBDA;
     }
 
-    void compile(const std::vector<Prim>& prims, std::vector<HostPass>* out) {
-        const int nq = in->nq;
+    std::vector<ScanItem> items_of(const std::vector<Prim>& prims) const {
         const int n = (int)prims.size();
         std::vector<ScanItem> items(n);
         for (int i = 0; i < n; ++i) {
@@ -920,6 +953,13 @@ struct Compiler {
                 items[i] = {p.gk == Prim::GPHASE ? IT_PHASE : IT_GATE, p.bit, p.bit2, p.gk == Prim::GSWAP,
                             !(backward && p.gk == Prim::GD4)};
         }
+        return items;
+    }
+
+    void compile(const std::vector<Prim>& prims, std::vector<HostPass>* out) {
+        const int nq = in->nq;
+        const int n = (int)prims.size();
+        const std::vector<ScanItem> items = items_of(prims);
         // The large-stride preference only breaks ties between equally useful tile
         // bits; where it nevertheless costs passes (two-qubit gates on neighbouring
         // qubits, whose single bits are all "half useful"), this compile drops it.
@@ -1151,6 +1191,25 @@ Prim mat4_prim(Plan* plan, int nq, int is1, int is2, const double* m, Prim::GKin
 const double kSwap4[32] = {1, 0, 0, 0, 0, 0, 0, 0,  0, 0, 0, 0, 1, 0, 0, 0,
                            0, 0, 1, 0, 0, 0, 0, 0,  0, 0, 0, 0, 0, 0, 1, 0};
 
+// Forward passes of a single-instance plan with tiles of 2^tile amplitudes and rb
+// register bits.
+int forward_passes(Plan* plan, int tile, int rb) {
+    Instance& in = plan->inst[0];
+    std::map<std::string, std::vector<int>> cuts;
+    Compiler c;
+    c.cut_cache = &cuts;
+    c.plan = plan;
+    c.in = &in;
+    c.backward = false;
+    c.k = std::min(tile, in.nq);
+    c.C = std::min(plan->tiling.carrier_bits, c.k);
+    c.RBITS = rb;
+    c.RB = std::min(rb, c.k);
+    const std::vector<ScanItem> items = c.items_of(in.prims);
+    const int cap = plan->tiling.page_cap, n = c.count_passes(items, cap);
+    return cap > 0 ? std::min(n, c.count_passes(items, 0)) : n;
+}
+
 std::string fmt(const char* f, long long a = 0, long long b = 0) {
     char buf[256];
     std::snprintf(buf, sizeof buf, f, a, b);
@@ -1158,6 +1217,8 @@ std::string fmt(const char* f, long long a = 0, long long b = 0) {
 }
 
 }  // namespace
+
+static void choose_tiling(Plan* plan);
 
 int compile_plan(Plan* plan, const pk_problem* probs, int n_inst, int prec, std::string* err) {
     if (prec != PK_FP64 && prec != PK_FP32) {
@@ -1358,7 +1419,100 @@ int compile_plan(Plan* plan, const pk_problem* probs, int n_inst, int prec, std:
     }
     plan->n_d2 = d2;
     plan->total_elems = off;
+    choose_tiling(plan);
     return recompile(plan, err);
+}
+
+// Tile and register bits of a single-instance plan that the caller leaves to the
+// library.  A tile of 2^13 amplitudes (128 KB in FP64) takes a CU's LDS and so most
+// of its time moves one tile after the other; it pays where it saves passes.  Measured
+// per call (us), G a noisy Grover iteration, Q the Fourier transform of 2/3 of the
+// qubits, T a two-qubit gate on every neighbouring pair; kX/rY: tiles of 2^X, Y
+// register bits:
+//  * up to 2^20 amplitudes the state gives few tiles, and smaller ones with 8
+//    amplitudes a thread (more, shorter waves) shorten every step of the one chain of
+//    latencies that a workgroup then is.  FP64 (13/4 -> chosen): G 9 15.8 -> 12.8,
+//    G 16 32.5 -> 24.9, G 18 38.9 -> 30.5, G 20 55.8 -> 49.0 (k12/r4), Q 18 39.1 ->
+//    31.6.  FP32 (13/5 ->): G 12 21.2 -> 13.5, G 16 34.6 -> 23.4, Q 20 82.5 -> 42.9.
+//    4x4 steps keep 16 amplitudes a thread, which hold two qubit pairs a stage: FP64
+//    T 16 49.5 -> 35.8, FP32 T 16 55.8 -> 37.1, T 20 78.1 -> 61.8.
+//  * above, 2^12 tiles leave two workgroups a CU, which hide each other's latencies,
+//    but more passes cost more than that: FP64 G 24 495 -> 451, G 27 4276 -> 4435
+//    (HBM-bound, equal passes); Q 24 439 -> 400, Q 26 (one pass more) 1708 -> 2074,
+//    Q 30 40290 -> 34819 (k12/r3); T 24 644 -> 613, T 27 (one more) 4789 -> 4616.
+//    FP32 phases take twice as long with 32 amplitudes a thread (Q 28: 13/5 9654,
+//    k12/r4 5107).
+static void choose_tiling(Plan* plan) {
+    Tiling& t = plan->tiling;
+    if (plan->inst.size() != 1 || !t.automatic) return;
+    const Instance& in = plan->inst[0];
+    const int nq = in.nq, big = default_tile_bits(plan->prec), rb0 = default_reg_bits(plan->prec);
+    const bool fp64 = plan->prec == PK_FP64;
+    bool mat4 = false, phase = false;
+    for (const Prim& p : in.prims) {
+        phase = phase || (p.kind == Prim::GATE && p.gk == Prim::GPHASE);
+        mat4 = mat4 || (p.kind == Prim::GATE && p.bit2 >= 0 && p.gk != Prim::GPHASE && p.gk != Prim::GSWAP);
+    }
+    if (nq <= 12) {
+        t.reg_bits = mat4 ? 4 : 3;
+    } else if (nq == 13) {
+        // one 2^13 tile, or eight of 2^10: FP64 G 22.8 and 22.2, T 36.1 and 27.1; FP32 G 19.7
+        // (r4) and 21.5
+        const bool one = !fp64 && !mat4 && !phase;
+        t.tile_bits = one ? big : 10;
+        t.reg_bits = one || mat4 ? 4 : 3;
+    } else if (nq <= 20) {
+        // the smallest tile that takes no more passes (two tiles with 4 common bits cover
+        // the state from (nq + 4) / 2 on)
+        int k = std::max(10, (nq + 5) / 2);
+        if (mat4 || phase) {
+            const bool more = nq > 18 && !mat4;  // 2^12 tiles even for a pass more
+            const int most = more ? 1 << 30 : forward_passes(plan, big, mat4 ? 4 : rb0);
+            if (more) k = 12;
+            while (k < big && forward_passes(plan, k, mat4 ? 4 : 3) > most) ++k;
+        }
+        t.tile_bits = k;
+        t.reg_bits = mat4 || (fp64 && k >= 12 && !phase) ? 4 : 3;
+    } else if (phase && !mat4 && fp64) {
+        const bool small = nq <= 22 || forward_passes(plan, 12, 4) <= forward_passes(plan, big, 4);
+        t.tile_bits = small ? 12 : big;
+        t.reg_bits = small && (nq <= 22 || nq >= 27) ? 3 : 4;
+    } else if (phase && !mat4) {
+        t.reg_bits = 4;
+        if (forward_passes(plan, 12, 4) <= forward_passes(plan, big, 4)) t.tile_bits = 12;
+    } else if (mat4) {
+        t.reg_bits = 4;
+        if (forward_passes(plan, 12, 4) <= forward_passes(plan, big, 4) + (nq >= 23 ? 1 : 0)) t.tile_bits = 12;
+    } else if (fp64) {
+        if (nq >= 23 && nq <= 25 && forward_passes(plan, 12, 4) <= forward_passes(plan, big, 4)) t.tile_bits = 12;
+    } else if (nq == 21) {
+        t.reg_bits = 4;
+    }
+}
+
+// The tile walk of a pass that the caller leaves to the library.  At n_q = 30 (2^17
+// tiles) runs of two take the five passes of an FP64 iteration from 34.1 to 33.4 ms and
+// the Fourier transform from 40.3 to 39.2; with fewer tiles no walk is the faster one
+// (n_q = 29: 16.8 strided, 17.5 runs of two; n_q = 27: 4.31, 4.26).
+static int32_t default_walk(const Plan* plan, const HostPass& hp) {
+    return plan->prec == PK_FP64 && hp.k == 13 && hp.ntiles >= (int64_t)1 << 17 ? 2 : 0;
+}
+
+// The overlapped tile loop of such a pass: where there are exchanges to overlap and at
+// least four tiles a workgroup (it reads one tile more than it works on).  FP64, 2^13
+// tiles, default and overlapped loop (us): n_q = 22 109 and 113, 23 280 and 266, 26 2198
+// and 2114, 30 34.1 and 33.4 ms; a streamed pass of 2^16 tiles or more loses (n_q = 29
+// 3158 and 3299).  At 2^12 tiles two workgroups a CU overlap anyway: Hadamard passes
+// lose (n_q = 24 451 and 461) below 2^14 tiles, passes with phases or 4x4 steps gain
+// (416 and 400, 628 and 613; FP32 489 and 467).
+static int32_t default_overlap(const Plan* plan, const HostPass& hp) {
+    if (hp.rbits != 4 || hp.stages.size() < 2 || hp.ntiles < 1024 || hp.k < 12) return 0;
+    if (hp.flags & PASS_STREAM) return hp.ntiles < (1 << 16);
+    bool heavy = !hp.phases.empty();
+    for (const HostStage& hs : hp.stages)
+        for (const Op& o : hs.ops) heavy = heavy || o.kind == OP_MAT4;
+    if (plan->prec != PK_FP64) return heavy;
+    return heavy || hp.k == 13 || hp.ntiles >= (1 << 14);
 }
 
 int recompile(Plan* plan, std::string* err) {
@@ -1477,9 +1631,9 @@ int recompile(Plan* plan, std::string* err) {
             if (plan->prec == PK_FP64 && (hp.flags & PASS_LAST) && bytes >= kStreamBytes && hp.sbits == hp.tbits)
                 hp.flags |= PASS_STREAM;
             emit(plan->inst[i], (int)i, hp);
-            if (i == 0 && plan->inst.size() == 1 && p < plan->walk.size()) plan->passes.back().walk = plan->walk[p];
-            if (i == 0 && plan->inst.size() == 1 && p < plan->overlap.size())
-                plan->passes.back().overlap = plan->overlap[p];
+            if (plan->inst.size() != 1) continue;
+            plan->passes.back().walk = plan->walk.empty() ? default_walk(plan, hp) : plan->walk[p];
+            plan->passes.back().overlap = plan->overlap.empty() ? default_overlap(plan, hp) : plan->overlap[p];
         }
     plan->n_fwd_passes = (int)plan->passes.size();
     for (size_t i = 0; i < plan->inst.size(); ++i)

@@ -75,6 +75,8 @@ struct Tiling {
     int reg_bits = 4;    // register bits per thread in forward passes (4 or 5)
     int lane_order = 1;  // 1: lanes cover tile bits of good DRAM stride next to the carriers
     int page_cap = 0;    // >0: prefer at most this many tile bits at >= 2 MiB byte stride
+    bool automatic = true; // tile and register bits follow the size and the gates (until the
+                           // caller sets either)
 };
 
 // log2 of the page size the per-CU address translation cache works in (2 MiB).
