@@ -164,6 +164,9 @@ class Plan:
         _check(lib().pk_create(arr, len(problems), self.prec, ctypes.byref(h)))
         self.handle = h
         self._ws = {}
+        # fixed by the problems: amplitudes in all, doubles of an angle array
+        self.n_elem = self.offsets()[-1]
+        self._n_angle_values = 3 * self.n_angles()
 
     def close(self):
         if getattr(self, "handle", None):
@@ -264,12 +267,12 @@ class Plan:
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()  # ctypes takes an int for a void pointer
 
 
 def _stream(device):
     import torch
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    return torch.cuda.current_stream(device).cuda_stream
 
 
 def _check_state(plan, t, nelem, name):
@@ -291,10 +294,10 @@ def _check_f64(t, n, name, device):
 
 def evaluate_into(plan, psi_in, psi_out, L_out, norm_out=None, angles=None):
     """pk_evaluate on preallocated device tensors (L_out, norm_out: float64 [1])."""
-    nelem = plan.offsets()[-1]
+    nelem = plan.n_elem
     _check_f64(L_out, 1, "L_out", psi_in.device)
     _check_f64(norm_out, 1, "norm_out", psi_in.device)
-    _check_f64(angles, 3 * plan.n_angles(), "angles", psi_in.device)
+    _check_f64(angles, plan._n_angle_values, "angles", psi_in.device)
     _check_state(plan, psi_in, nelem, "psi_in")
     _check_state(plan, psi_out, nelem, "psi_out")
     ws = plan.workspace(PK_OP_EVAL, psi_in.device)
@@ -307,10 +310,10 @@ def evaluate_static(plan, psi_in, psi_out, L_out, norm_out=None, angles=None):
     """pk_evaluate_static: pk_evaluate with the library's static workspace, on
     preallocated device tensors; allocates nothing (the plan's tables must already
     be on the device, e.g. after one ``evaluate``)."""
-    nelem = plan.offsets()[-1]
+    nelem = plan.n_elem
     _check_f64(L_out, 1, "L_out", psi_in.device)
     _check_f64(norm_out, 1, "norm_out", psi_in.device)
-    _check_f64(angles, 3 * plan.n_angles(), "angles", psi_in.device)
+    _check_f64(angles, plan._n_angle_values, "angles", psi_in.device)
     _check_state(plan, psi_in, nelem, "psi_in")
     _check_state(plan, psi_out, nelem, "psi_out")
     rc = lib().pk_evaluate_static(plan.handle, _ptr(psi_in), _ptr(psi_out), _ptr(L_out), _ptr(norm_out),
@@ -334,10 +337,10 @@ def evaluate_repeat(plan, psi_in, reps, angles=None, want_norm=True, out=None):
     import torch
     dev = psi_in.device
     psi_out = torch.empty_like(psi_in) if out is None else out
-    nelem = plan.offsets()[-1]
+    nelem = plan.n_elem
     _check_state(plan, psi_in, nelem, "psi_in")
     _check_state(plan, psi_out, nelem, "psi_out")
-    _check_f64(angles, 3 * plan.n_angles(), "angles", dev)
+    _check_f64(angles, plan._n_angle_values, "angles", dev)
     L = torch.empty(1, dtype=torch.float64, device=dev)
     norm = torch.empty(1, dtype=torch.float64, device=dev) if want_norm else None
     ws = plan.workspace(PK_OP_EVAL, dev)
@@ -383,14 +386,14 @@ def grover_iterations(nq):
 def evaluate_batched(plan, psi_in, angles=None, want_norm=True, out=None):
     """All instances in one persistent launch; states packed at plan.offsets()."""
     import torch
-    nelem = plan.offsets()[-1]
+    nelem = plan.n_elem
     _check_state(plan, psi_in, nelem, "psi_in")
     dev = psi_in.device
     psi_out = torch.empty_like(psi_in) if out is None else out
     _check_state(plan, psi_out, nelem, "psi_out")
     L = torch.empty(plan.n_inst, dtype=torch.float64, device=dev)
     norm = torch.empty(plan.n_inst, dtype=torch.float64, device=dev) if want_norm else None
-    _check_f64(angles, 3 * plan.n_angles(), "angles", dev)
+    _check_f64(angles, plan._n_angle_values, "angles", dev)
     ws = plan.workspace(PK_OP_EVAL, dev)
     rc = lib().pk_evaluate_batched(plan.handle, _ptr(psi_in), _ptr(psi_out), _ptr(L), _ptr(norm), _ptr(angles),
                                    _ptr(ws), _stream(dev))
@@ -401,29 +404,29 @@ def evaluate_batched(plan, psi_in, angles=None, want_norm=True, out=None):
 def backward(plan, psi_out, dL, angles=None):
     """pk_backward: returns (grad_psi_in, grad_angles) for the scalar sum dL * L."""
     import torch
-    nelem = plan.offsets()[-1]
+    nelem = plan.n_elem
     _check_state(plan, psi_out, nelem, "psi_out")
     dev = psi_out.device
     _check_f64(dL, plan.n_inst, "dL", dev)
-    _check_f64(angles, 3 * plan.n_angles(), "angles", dev)
+    _check_f64(angles, plan._n_angle_values, "angles", dev)
     grad_psi = torch.empty_like(psi_out)
-    n_d2 = plan.n_angles()
-    grad_ang = torch.zeros(max(1, 3 * n_d2), dtype=torch.float64, device=dev)
+    # pk_backward writes the three gradients of every rotation
+    grad_ang = torch.empty(plan._n_angle_values, dtype=torch.float64, device=dev)
     ws = plan.workspace(PK_OP_BACKWARD, dev)
-    rc = lib().pk_backward(plan.handle, _ptr(psi_out), _ptr(dL), _ptr(grad_psi), _ptr(grad_ang) if n_d2 else None,
-                           _ptr(angles), _ptr(ws), _stream(dev))
+    rc = lib().pk_backward(plan.handle, _ptr(psi_out), _ptr(dL), _ptr(grad_psi),
+                           _ptr(grad_ang) if plan._n_angle_values else None, _ptr(angles), _ptr(ws), _stream(dev))
     _check(rc, plan.handle)
-    return grad_psi, grad_ang[:3 * n_d2]
+    return grad_psi, grad_ang
 
 
 def time_passes(plan, psi_in, psi_out, angles=None):
     """Per-pass kernel durations (ms) of one evaluation, from HIP events on the current stream."""
     import torch
     dev = psi_in.device
-    nelem = plan.offsets()[-1]
+    nelem = plan.n_elem
     _check_state(plan, psi_in, nelem, "psi_in")
     _check_state(plan, psi_out, nelem, "psi_out")
-    _check_f64(angles, 3 * plan.n_angles(), "angles", dev)
+    _check_f64(angles, plan._n_angle_values, "angles", dev)
     L = torch.empty(1, dtype=torch.float64, device=dev)
     ws = plan.workspace(PK_OP_EVAL, dev)
     ms = (ctypes.c_double * 64)()
@@ -536,6 +539,9 @@ def _autograd_function():
                                      angles=angles.detach().contiguous() if angles is not None else None,
                                      want_norm=False)
             ctx.plan = plan
+            # an output without a gradient gets None, not a zero tensor of the state's size
+            # that would have to be written and looked through
+            ctx.set_materialize_grads(False)
             ctx.save_for_backward(psi_out, angles if angles is not None else torch.empty(0))
             ctx.has_angles = angles is not None
             return L[0], psi_out
@@ -545,7 +551,10 @@ def _autograd_function():
             if dpsi_out is not None and bool(torch.any(dpsi_out != 0)):
                 raise NotImplementedError("gradients flow from L only; psi_out is returned for inspection")
             psi_out, angles = ctx.saved_tensors
-            dl = dL.detach().reshape(1).to(torch.float64).contiguous()
+            if dL is None:
+                dl = torch.zeros(1, dtype=torch.float64, device=psi_out.device)
+            else:
+                dl = dL.detach().reshape(1).to(torch.float64).contiguous()
             gpsi, gang = backward(ctx.plan, psi_out, dl, angles=angles if ctx.has_angles else None)
             return gpsi, (gang if ctx.has_angles else None), None
 

@@ -133,3 +133,41 @@ def test_readouts_at_the_combine_limit(nq, tile, marks, prec):
         tol = (1 << nq) * 2.0 ** -52 + (2.0 ** -22 if prec == "fp32" else 0.0)
         assert abs(L.item() - math.fsum(p[marked])) <= tol * math.fsum(p[marked])
         assert abs(norm.item() - math.fsum(p)) <= tol * math.fsum(p)
+
+
+@pytest.mark.parametrize("angles", [False, True])
+def test_autograd_outputs_without_a_gradient(angles):
+    """The unused output of grover_eval gets no gradient tensor: a loss of L alone equals
+    pk_backward; one of psi_out alone whose gradient is zero gives zeros; any other
+    gradient of psi_out stays refused."""
+    pk = _pk()
+    nq = 9
+    plan = pk.Plan({"nq": nq, "gates": W.grover_gates((2, 2, 0.5, 0.8, 0.0)), "marked": [5, 99]})
+    x = torch.from_numpy(_state(nq, 4)).to("cuda").requires_grad_(True)
+    a = torch.tensor([0.5, 0.8, 0.1], dtype=torch.float64, device="cuda", requires_grad=True) if angles else None
+    L, out = pk.grover_eval(plan, x, a)
+    wrt = [x] + ([a] if angles else [])
+    got = torch.autograd.grad(3.0 * L, wrt)
+    want = pk.backward(plan, out.detach(), torch.full((1,), 3.0, dtype=torch.float64, device="cuda"),
+                       angles=a.detach() if angles else None)
+    assert all(torch.equal(g, w) for g, w in zip(got, want))
+    L, out = pk.grover_eval(plan, x, a)
+    zero = torch.autograd.grad((0.0 * out.abs()).sum(), wrt)
+    assert all(not torch.any(g != 0) for g in zero)
+    L, out = pk.grover_eval(plan, x, a)
+    with pytest.raises(NotImplementedError):
+        torch.autograd.grad(out.abs().sum(), wrt)
+
+
+def test_single_instance_batch_with_automatic_tiling():
+    """A one-instance plan goes through pk_evaluate_batched whatever register bits the
+    library picked (3 at these sizes); set by the caller, 3 stays refused."""
+    pk = _pk()
+    for nq in (3, 12, 16, 18):
+        plan = pk.Plan({"nq": nq, "gates": W.grover_gates((1, 3, 0.5, 0.8, 0.0)), "marked": [1, 6]})
+        x = torch.from_numpy(_state(nq, nq)).to("cuda")
+        a, b = pk.evaluate(plan, x), pk.evaluate_batched(plan, x)
+        assert all(torch.equal(u, v) for u, v in zip(a, b))
+        plan.set_launch(0, 3)
+        with pytest.raises(pk.PaperkernError):
+            pk.evaluate_batched(plan, x)

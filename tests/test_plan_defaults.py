@@ -1,0 +1,70 @@
+"""The library's own choice of tile and register bits for a single instance (CPU): the
+schedule it leads to computes what the oracle and an explicit tiling compute.
+"""
+
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_0902_0699_amd import paperkern as pk
+from paper_0902_0699_amd import workload as W
+from schedule_emulator import run_backward, run_forward
+
+
+def _gates(kind, nq, rng):
+    a, b = 1, nq
+    if kind == "hadamards":
+        return W.grover_gates((max(1, nq // 2), 3, 0.7, 0.4, 0.0))
+    if kind == "phases":
+        return W.phase_circuit(rng, nq, 12) + [("D2", b, 0.2, 0.9, 0.1)]
+    if kind == "qft":
+        return [("H", nq), ("QFT", 1, nq - 1), ("ORACLE",)]
+    u, _ = np.linalg.qr(rng.standard_normal((4, 4)) + 1j * rng.standard_normal((4, 4)))
+    return [("HALL",), ("TWOOP", a, b, u), ("D4", b, a, 0.3, 0.5, -0.2), ("SWAP", 1, 2), ("CNOT", 2, a), ("INV",),
+            ("HALL",)]
+
+
+@pytest.mark.parametrize("kind", ["hadamards", "phases", "qft", "two_qubit"])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("nq", [3, 9, 12, 13, 14, 15])
+def test_automatic_schedule_matches_the_oracle(nq, prec, kind):
+    rng = np.random.default_rng(nq)
+    gates = _gates(kind, nq, rng)
+    marked = [2, (1 << nq) - 1]
+    prob = {"nq": nq, "gates": gates, "marked": marked}
+    v = rng.standard_normal(1 << nq) + 1j * rng.standard_normal(1 << nq)
+    psi = v / np.linalg.norm(v)
+    want, Lw, _ = O.evaluate(nq, gates, marked, psi)
+    plan = pk.Plan(prob, prec=prec)
+    out, L = run_forward([prob], plan.describe(), 0, psi)
+    np.testing.assert_allclose(out, want, rtol=0, atol=1e-12)
+    assert abs(L - Lw) <= 1e-12
+    if prec == "fp64":
+        gpsi, gang = run_backward([prob], plan.describe(), 0, want, 0.5)
+        wpsi, wang = O.adjoint_grad(nq, gates, marked, psi, 0.5)
+        np.testing.assert_allclose(gpsi, wpsi, rtol=0, atol=1e-12)
+        np.testing.assert_allclose(gang.reshape(-1), np.asarray(wang).reshape(-1), rtol=0, atol=1e-12)
+
+
+@pytest.mark.parametrize("kind", ["hadamards", "phases", "qft", "two_qubit"])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("nq", [1, 6, 12, 13, 16, 18, 19, 20, 21, 22, 23, 24, 25, 26])
+def test_automatic_settings_stay_within_the_kernels(nq, prec, kind):
+    """Tiles of at most 2^13, 3 to 5 register bits, at most 1024 threads, two-qubit gates
+    with room for two pairs; setting either one restores the documented other."""
+    if nq < 3 and kind != "hadamards":
+        pytest.skip("needs three qubits")
+    gates = _gates(kind, nq, np.random.default_rng(nq))
+    plan = pk.Plan({"nq": nq, "gates": gates, "marked": [1]}, prec=prec)
+    d = plan.describe()
+    for p in d["instances"][0]["forward"]:
+        assert p["k"] <= min(13, nq) and p["rbits"] in (3, 4, 5) and d["tile_bits"] - p["rbits"] <= 10
+        assert kind != "two_qubit" or p["rbits"] == 4
+    assert all(p["rbits"] == 4 and p["k"] <= 12 for p in d["instances"][0]["backward"])
+    default = 4 if prec == "fp64" else 5
+    plan.set_tiling(11, 4)
+    assert {p["rbits"] for p in plan.describe()["instances"][0]["forward"]} == {default}
+    plan = pk.Plan({"nq": nq, "gates": gates, "marked": [1]}, prec=prec)
+    plan.set_launch(0, 0)
+    d = plan.describe()
+    assert d["tile_bits"] == 13 and {p["rbits"] for p in d["instances"][0]["forward"]} == {default}
