@@ -353,7 +353,8 @@ int pk_search_workspace_bytes(int64_t* bytes);
 
 /*
  * pk_evaluate_batched -- evaluate every instance of the plan ("multiverses",
- * Sec. 6.2) in one persistent launch (after one that clears its queue); a single
+ * Sec. 6.2) in one persistent launch (after one that clears its queue; with instances
+ * that are spread, see pk_set_batch, one more per pass and one for their readouts); a single
  * instance whose tiling is the library's choice runs as pk_evaluate does.  States are
  * packed at pk_plan_offsets(); L_out and norm_out (or NULL) hold n_inst doubles.
  * Other arguments as pk_evaluate.

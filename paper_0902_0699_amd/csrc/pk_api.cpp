@@ -158,6 +158,16 @@ int ensure_device(DevPlan* d) {
     std::vector<Reduction> rb = backward_reductions(&P);
     r.insert(r.end(), rb.begin(), rb.end());
     put(buf, t.red, r);
+    size_t o = t.spread;
+    for (const auto& l : P.team.levels) {
+        put(buf, o, l.pass);
+        o += l.pass.size() * sizeof(int32_t);
+        put(buf, o, l.first);
+        o += l.first.size() * sizeof(int32_t);
+    }
+    std::vector<Reduction> rs;
+    for (int32_t i : P.team.spread) rs.insert(rs.end(), r.begin() + 2 * i, r.begin() + 2 * i + 2);
+    put(buf, t.spread_red, rs);
     void* ptr = nullptr;
     e = hipMalloc(&ptr, t.total);
     if (e != hipSuccess) return hip_fail(d, e, "hipMalloc(plan tables)");
@@ -479,7 +489,28 @@ hipError_t enqueue_batched(DevPlan* d, const EvalArgs& a, hipStream_t st) {
     B.team_size = ts.team_size;
     B.n_xcd = ts.n_xcd;
     B.spin_ticks = d->spin_ticks;
-    return launch_batched(L, B, d->batch_grid, st);
+    // the first launch: teams, the spread instances' first passes, the queue; then their
+    // other passes, a launch each, and their readouts
+    size_t o = t.spread;
+    const size_t n = ts.levels.empty() ? 1 : ts.levels.size();
+    for (size_t l = 0; l < n; ++l) {
+        if (l < ts.levels.size()) {
+            const TeamSchedule::Level& v = ts.levels[l];
+            B.n_spread = (int32_t)v.pass.size();
+            B.spread_pass = at<int32_t>(P.d_tables, o);
+            o += v.pass.size() * sizeof(int32_t);
+            B.spread_first = at<int32_t>(P.d_tables, o);
+            o += v.first.size() * sizeof(int32_t);
+            B.spread_tiles = v.first.back();
+            B.spread_part = (B.spread_tiles + d->batch_grid - 1) / d->batch_grid;
+        }
+        e = launch_batched(L, B, d->batch_grid, st);
+        if (e != hipSuccess) return e;
+        B.n_solo = B.n_teams = 0;
+    }
+    if (ts.spread.empty()) return hipSuccess;
+    return launch_reduce(at<Reduction>(P.d_tables, t.spread_red), 2 * (int)ts.spread.size(),
+                         static_cast<double*>(a.ws), a.L_out, a.norm_out, nullptr, st);
 }
 
 struct BwdArgs {

@@ -53,6 +53,13 @@ struct BatchArgs {
     int32_t n_teams;
     int32_t team_size;
     int32_t n_xcd;
+    // spread instances: the passes of one level and the first tile of each in their
+    // common list (n_spread + 1 entries, the last the total), cut in parts of spread_part
+    const int32_t* spread_pass;
+    const int32_t* spread_first;
+    int32_t n_spread;
+    int64_t spread_tiles;
+    int64_t spread_part;
 };
 
 // Device arguments of the persistent repeat launch (see repeat_kernel).

@@ -1141,12 +1141,18 @@ __device__ __forceinline__ void finish_instance(const KArgs& a, const PK_CONST I
     __syncthreads();
 }
 
-// Multiverse batch in one persistent launch.  First the teams: the j-th
-// workgroup of XCD x (w = j * n_xcd + x) is member j mod team_size of team
-// (j / team_size) * n_xcd + x; a team walks the passes of its large instances
-// together, its members taking the tiles of each pass in turn, with a team
-// barrier between passes.  Then every workgroup takes whole instances from the
-// queue (largest first) and runs all their passes itself.
+// Multiverse batch.  The work of a workgroup comes in three phases:
+//  * teams: the j-th workgroup of XCD x (w = j * n_xcd + x) is member j mod team_size
+//    of team (j / team_size) * n_xcd + x; a team walks the passes of its large
+//    instances together, its members taking the tiles of each pass in turn, with a
+//    team barrier between passes;
+//  * spread instances: one pass (`level`) of each, their tiles one after another in
+//    one list that is cut into equal contiguous parts, one a workgroup; their next
+//    pass is the next launch of this kernel, so that no workgroup waits for another;
+//  * the queue: whole instances (largest first), all passes by one workgroup.
+// The first launch of a batch does all three, the later ones the spread instances'
+// remaining passes.  One call of run_tiles serves every phase: the kernel is half the
+// size of one with a call each.
 template <typename R, int KMAX, int RB>
 __global__ void __launch_bounds__(1 << (KMAX - RB)) batched_kernel(KArgs a, BatchArgs b) {
     using T = typename Cplx<R>::T;
@@ -1159,45 +1165,93 @@ __global__ void __launch_bounds__(1 << (KMAX - RB)) batched_kernel(KArgs a, Batc
     const int w = blockIdx.x;
     const int xcd = w % b.n_xcd, j = w / b.n_xcd;
     const int team = b.team_size > 0 ? (j / b.team_size) * b.n_xcd + xcd : b.n_teams;
+    const int member = b.team_size > 0 ? j % b.team_size : 0;
+
+    enum { TEAM, SPREAD, QUEUE };
+    int phase = SPREAD, q = 0, q1 = 0, inst = -1, p = 0;
+    bool ok = true, broken = false;
+    unsigned int target = 0;
     if (team < b.n_teams) {
-        const int member = j % b.team_size;
-        unsigned int target = 0;
-        bool broken = false;
-        const int q0 = cptr(b.team_off)[team], q1 = cptr(b.team_off)[team + 1];
-        for (int q = q0; q < q1; ++q) {
-            const int inst = cptr(b.team_list)[q];
-            const PK_CONST InstDesc* D = idesc + inst;
-            bool ok = true;
-            for (int p = 0; p < D->npass; ++p) {
-                const PK_CONST Pass* P = cptr(a.passes) + D->first_pass + p;
-                run_tiles<R, 1, KMAX, RB>(a, P, member, b.team_size, P->ntiles, lds, red);
-                target += (unsigned int)b.team_size;
-                const bool passed = team_barrier(b.bars + team, target, b.spin_ticks, broken, &flag);
-                broken = broken || !passed;
-                ok = ok && passed;
-            }
-            if (member == 0) finish_instance<NT>(a, D, inst, ok, b.L_out, b.norm_out, red);
-        }
+        phase = TEAM;
+        q = cptr(b.team_off)[team];
+        q1 = cptr(b.team_off)[team + 1];
     }
+    // this workgroup's part of the spread instances' tile list, and the entry it begins in
+    int64_t at = b.spread_part * w, end = at + b.spread_part;
+    if (end > b.spread_tiles) end = b.spread_tiles;
+    int entry = 0;
+    for (int lo = 0, hi = b.n_spread; at < end && hi - lo > 1;) {
+        const int mid = (lo + hi) / 2;
+        if (cptr(b.spread_first)[mid] <= at) lo = mid;
+        else hi = mid;
+        entry = lo;
+    }
+
     for (;;) {
-        if (threadIdx.x == 0) item = (int)atomicAdd(b.queue, 1u);
-        __syncthreads();
-        const int it = item;
-        __syncthreads();
-        if (it >= b.n_solo) break;
-        const int inst = cptr(b.order)[it];
-        const PK_CONST InstDesc* D = idesc + inst;
-        for (int p = 0; p < D->npass; ++p) {
-            const PK_CONST Pass* P = cptr(a.passes) + D->first_pass + p;
-            warm_pass(a, P, P->stage_begin, P->nstages);
-            run_tiles<R, 1, KMAX, RB>(a, P, 0, 1, P->ntiles, lds, red);
+        // ---- the next tiles: `first`, `first` + stride, ... below `limit` of pass P
+        int pass = 0;
+        int64_t first = 0, stride = 1, limit = -1;
+        if (phase == TEAM) {
+            if (q >= q1) {
+                phase = SPREAD;
+                continue;
+            }
+            inst = cptr(b.team_list)[q];
+            pass = idesc[inst].first_pass + p;
+            first = member;
+            stride = b.team_size;
+        } else if (phase == SPREAD) {
+            if (at >= end) {
+                phase = QUEUE;
+                inst = -1;
+                continue;
+            }
+            pass = cptr(b.spread_pass)[entry];
+            const int64_t base = cptr(b.spread_first)[entry], next = cptr(b.spread_first)[entry + 1];
+            first = at - base;
+            limit = (end < next ? end : next) - base;
+            at = base + limit;
+            ++entry;
+        } else {
+            if (inst < 0) {
+                if (threadIdx.x == 0) item = (int)atomicAdd(b.queue, 1u);
+                __syncthreads();
+                const int it = item;
+                __syncthreads();
+                if (it >= b.n_solo) break;
+                inst = cptr(b.order)[it];
+                p = 0;
+            }
+            pass = idesc[inst].first_pass + p;
+        }
+        const PK_CONST Pass* P = cptr(a.passes) + pass;
+        warm_pass(a, P, P->stage_begin, P->nstages);
+        if (limit < 0) limit = P->ntiles;
+        run_tiles<R, 1, KMAX, RB>(a, P, first, stride, limit, lds, red);
+
+        // ---- what follows them
+        if (phase == TEAM) {
+            target += (unsigned int)b.team_size;
+            const bool passed = team_barrier(b.bars + team, target, b.spin_ticks, broken, &flag);
+            broken = broken || !passed;
+            ok = ok && passed;
+            if (++p < idesc[inst].npass) continue;
+            if (member == 0) finish_instance<NT>(a, idesc + inst, inst, ok, b.L_out, b.norm_out, red);
+            p = 0;
+            ok = true;
+            ++q;
+        } else if (phase == QUEUE) {
             // this workgroup's stores must be visible to its own loads of the next pass:
             // every wave waits for its stores to complete before the barrier
             __builtin_amdgcn_s_waitcnt(0);
             __threadfence_block();
             __syncthreads();
+            if (++p < idesc[inst].npass) continue;
+            finish_instance<NT>(a, idesc + inst, inst, true, b.L_out, b.norm_out, red);
+            inst = -1;
+        } else {
+            __syncthreads();  // the next entry's tiles reuse the LDS
         }
-        finish_instance<NT>(a, D, inst, true, b.L_out, b.norm_out, red);
     }
 }
 

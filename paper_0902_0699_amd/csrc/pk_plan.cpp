@@ -1676,11 +1676,27 @@ TeamSchedule team_schedule(const Plan* plan, int64_t grid, int n_xcd) {
     ts.n_teams -= ts.n_teams % n_xcd;
     std::vector<std::vector<int32_t>> lists(ts.n_teams);
     std::vector<double> load(ts.n_teams, 0.0);
+    auto tiles = [&](const Instance& in) {
+        int64_t t = 0;
+        for (const HostPass& hp : in.fwd) t += hp.ntiles;
+        return t;
+    };
+    auto is_large = [&](const Instance& in) {
+        return ts.n_teams > 0 && in.fwd.front().ntiles >= (int64_t)plan->batch.min_team_tiles * S;
+    };
+    int64_t total = 0;
+    for (const Instance& in : plan->inst)
+        if (!is_large(in)) total += tiles(in);
     for (int32_t i : plan->order) {
         const Instance& in = plan->inst[i];
-        const bool large = ts.n_teams > 0 && in.fwd.front().ntiles >= (int64_t)plan->batch.min_team_tiles * S;
-        if (!large) {
-            ts.solo.push_back(i);
+        if (!is_large(in)) {
+            // An instance of more than half an even share of all the tiles would leave
+            // the other workgroups waiting for the one that takes it whole.
+            // (The lists count tiles in 32 bits.)
+            if (in.fwd.size() > 1 && total < (int64_t)1 << 31 && 2 * grid * tiles(in) > total)
+                ts.spread.push_back(i);
+            else
+                ts.solo.push_back(i);
             continue;
         }
         int best = 0;
@@ -1688,6 +1704,16 @@ TeamSchedule team_schedule(const Plan* plan, int64_t grid, int n_xcd) {
             if (load[t] < load[best]) best = t;
         lists[best].push_back(i);
         load[best] += (double)in.fwd.size() * (double)((int64_t)1 << in.nq);
+    }
+    for (int32_t i : ts.spread) {
+        const Instance& in = plan->inst[i];
+        if (ts.levels.size() < in.fwd.size()) ts.levels.resize(in.fwd.size());
+        for (size_t p = 0; p < in.fwd.size(); ++p) {
+            TeamSchedule::Level& l = ts.levels[p];
+            if (l.first.empty()) l.first.push_back(0);
+            l.pass.push_back(plan->idesc[i].first_pass + (int32_t)p);
+            l.first.push_back(l.first.back() + (int32_t)in.fwd[p].ntiles);
+        }
     }
     ts.team_off.push_back(0);
     for (auto& l : lists) {
@@ -1732,6 +1758,11 @@ TableLayout table_layout(const Plan* plan) {
     o = align256(o + (size_t)(2 * plan->n_static + 5 * plan->n_d2) * 8 * sizeof(double));
     t.built4 = o;
     o = align256(o + (size_t)(2 * plan->n_static4 + 5 * plan->n_d4) * 32 * sizeof(double));
+    t.spread = o;  // per level of the spread instances: passes, then first tiles
+    for (const auto& l : plan->team.levels) o += (l.pass.size() + l.first.size()) * sizeof(int32_t);
+    o = align256(o);
+    t.spread_red = o;  // their evaluation reductions
+    o = align256(o + 2 * plan->team.spread.size() * sizeof(Reduction));
     t.ticket = o;  // workgroups done of a last pass that combines its readouts
     o = align256(o + sizeof(uint32_t));
     t.total = std::max<size_t>(o, 256);

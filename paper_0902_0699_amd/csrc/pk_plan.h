@@ -117,7 +117,14 @@ struct TeamSchedule {
     int n_xcd = 1;
     std::vector<int32_t> team_off;   // n_teams + 1 offsets into team_list
     std::vector<int32_t> team_list;  // the large instances of each team, largest first
-    std::vector<int32_t> solo;       // the rest, largest first (the queue's order)
+    std::vector<int32_t> solo;       // taken whole from the queue, largest first
+    // instances spread over every workgroup, pass after pass: per level the passes
+    // (Plan::passes) and where the tiles of each begin in the level's list
+    std::vector<int32_t> spread;     // the instances
+    struct Level {
+        std::vector<int32_t> pass, first;  // first: one entry more, the level's tiles
+    };
+    std::vector<Level> levels;
 };
 
 // Teams for a persistent grid of `grid` workgroups dispatched round-robin over
@@ -180,7 +187,7 @@ std::string describe(const Plan* plan);
 // Byte offsets of the device table arrays inside plan->d_tables.
 struct TableLayout {
     size_t passes, stages, phases, twid, urefs, mats, mats4, params, idesc, order, team_off, team_list, red, built, built4,
-        ticket, total;
+        ticket, spread, spread_red, total;
 };
 TableLayout table_layout(const Plan* plan);
 

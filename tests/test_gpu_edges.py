@@ -171,3 +171,45 @@ def test_single_instance_batch_with_automatic_tiling():
         plan.set_launch(0, 3)
         with pytest.raises(pk.PaperkernError):
             pk.evaluate_batched(plan, x)
+
+
+# Instances of more than half an even share of the tiles are spread over every
+# workgroup, pass after pass, the others taken whole: only spread ones, only whole ones,
+# both, sizes whose lists end inside a workgroup's part, and a team's beside them.
+@pytest.mark.parametrize("prec,sizes,tile,team", [
+    ("fp64", [15], 8, 0), ("fp64", [14, 16, 5, 13], 9, 0), ("fp32", [16, 3, 14, 15, 9], 10, 0),
+    ("fp64", [10] * 600, 10, 0), ("fp64", [15, 13] + [8, 9, 10] * 40, 8, 0), ("fp32", [15, 13] + [8, 9, 10] * 40, 8, 0),
+    ("fp64", [17, 13, 11, 12], 8, 16)])
+def test_batch_with_spread_instances(prec, sizes, tile, team):
+    """Every instance's state, L and norm against pk_evaluate on it alone (the same
+    passes and tiles, so the states agree bit for bit; the readouts add the same
+    partials in another order: n 2^-53 relative), twice, with and without the norm."""
+    pk = _pk()
+    rng = np.random.default_rng(len(sizes))
+    dt = torch.complex128 if prec == "fp64" else torch.complex64
+    probs = []
+    for nq in sizes:
+        gates = W.grover_gates((int(rng.integers(1, nq + 1)), int(rng.integers(5)), 0.3, 0.9, 0.0))
+        if nq > 4:
+            gates += [("CPHASEK", 1, nq, 3), ("CNOT", 2, nq - 1)]
+        probs.append({"nq": nq, "gates": gates, "marked": sorted({int(rng.integers(1 << nq)), 1})})
+    print("batch %s %s tile %d team %d" % (prec, sizes[:6], tile, team), flush=True)
+    plan = pk.Plan(probs, prec=prec)
+    plan.set_tiling(tile, 3)
+    plan.set_launch(0, 4)
+    plan.set_batch(team, 4)
+    offs = plan.offsets()
+    x = torch.from_numpy(np.concatenate([_state(nq, 7 + i % 9) for i, nq in enumerate(sizes)])).to(dt).to("cuda")
+    for want_norm in (True, False):
+        out, L, norm = pk.evaluate_batched(plan, x, want_norm=want_norm)
+        for i in range(0, len(sizes), 1 if len(sizes) < 50 else 37):
+            one = pk.Plan(probs[i], prec=prec)
+            one.set_tiling(tile, 3)
+            one.set_launch(0, 4)
+            psi, l1, n1 = pk.evaluate(one, x[offs[i]:offs[i + 1]].clone())
+            assert torch.equal(psi, out[offs[i]:offs[i + 1]]), i
+            tol = (1 << sizes[i]) * 2.0 ** -53 + 2.0 ** -50
+            assert abs(L[i].item() - l1.item()) <= tol * l1.item()
+            # FP32 norm partials: terms whose rounding the two kernels may contract differently
+            ntol = tol + (2.0 ** -22 if prec == "fp32" else 0.0)
+            assert not want_norm or abs(norm[i].item() - n1.item()) <= ntol * n1.item()
