@@ -132,15 +132,15 @@ __device__ __forceinline__ RegBits reg_slots(const Layout& L) {
     return b;
 }
 
-// State offsets (elements) of a stage used for HBM access: the thread's part and
-// the uniform parts of the register bits.  They are OR-sums of the plan's per-bit
+// State offsets of a stage used for HBM access: the thread's part (elements) and the
+// uniform parts of the register bits (bytes).  They are sums of the plan's per-bit
 // offsets; `TB` is the number of thread-index bits.
 struct GOff {
     uint32_t gt;
     int64_t g[kMaxRegBits];
 };
 
-template <int TB>
+template <int ESZ, int TB>
 __device__ __forceinline__ GOff make_goff(const PK_CONST uint32_t* thr, const PK_CONST uint32_t* reg, unsigned tid) {
     GOff G;
     uint32_t g = 0u;
@@ -148,13 +148,18 @@ __device__ __forceinline__ GOff make_goff(const PK_CONST uint32_t* thr, const PK
     for (int i = 0; i < TB; ++i) g |= (0u - ((tid >> i) & 1u)) & thr[i];
     G.gt = g;
 #pragma unroll
-    for (int a = 0; a < kMaxRegBits; ++a) G.g[a] = reg[a];
+    for (int a = 0; a < kMaxRegBits; ++a) G.g[a] = (int64_t)reg[a] * ESZ;
     return G;
 }
 
-__device__ __forceinline__ int64_t goff(const GOff& G, int i) {
-    return ((i & 1) ? G.g[0] : 0) + ((i & 2) ? G.g[1] : 0) + ((i & 4) ? G.g[2] : 0) + ((i & 8) ? G.g[3] : 0) +
-           ((i & 16) ? G.g[4] : 0);
+// Byte offsets of the NR registers of a tile that begins at element `base`: each is
+// another's plus one bit's, a 64-bit addition (summed up from the bits for every
+// access, the scalar instructions took ~75 ns a load where a pass is one tile long).
+template <int ESZ, int NR>
+__device__ __forceinline__ void reg_offsets(const GOff& G, int64_t base, int64_t (&u)[NR]) {
+    u[0] = base * ESZ;
+#pragma unroll
+    for (int i = 1; i < NR; ++i) u[i] = u[i & (i - 1)] + G.g[__builtin_ctz(i)];
 }
 
 // ---------------------------------------------------------------------------- gate bodies
@@ -514,7 +519,7 @@ struct PassCtx {
 };
 
 // What the first tile's loads need: read from the pass record alone.
-template <int KMAX, int RB>
+template <int ESZ, int KMAX, int RB>
 __device__ __forceinline__ PassCtx make_ctx(const PK_CONST Pass* P) {
     PassCtx C;
     const int k = P->k;
@@ -524,8 +529,8 @@ __device__ __forceinline__ PassCtx make_ctx(const PK_CONST Pass* P) {
     C.nstages = P->nstages;
     const unsigned nact = k >= RB ? (1u << (k - RB)) : 1u;
     C.active = threadIdx.x < nact;
-    C.G0 = make_goff<KMAX - RB>(P->lthr, P->lreg, threadIdx.x);
-    C.Gl = make_goff<KMAX - RB>(P->sthr, P->sreg, threadIdx.x);
+    C.G0 = make_goff<ESZ, KMAX - RB>(P->lthr, P->lreg, threadIdx.x);
+    C.Gl = make_goff<ESZ, KMAX - RB>(P->sthr, P->sreg, threadIdx.x);
     return C;
 }
 
@@ -545,9 +550,9 @@ __device__ __forceinline__ void warm_pass(const KArgs& a, const PK_CONST Pass* P
 }
 
 // A copy of the register offsets that the compiler takes as new: their sums over
-// register bits are then added up for each tile (two scalar instructions a load)
-// instead of hoisted out of the tile loop, where up to 64 of them held scalar
-// registers and were spilled to vector lanes.
+// register bits are then added up for each tile (one addition a load) instead of
+// hoisted out of the tile loop, where up to 64 of them held scalar registers and were
+// spilled to vector lanes.
 __device__ __forceinline__ GOff opaque(const GOff& g) {
     GOff o = g;
 #pragma unroll
@@ -598,27 +603,28 @@ __device__ __forceinline__ void load_tile(const KArgs& a, const PassCtx& C, int6
     const char* in1 = reinterpret_cast<const char*>(a.dst1);
     const bool read1 = NV == 2 && !(C.flags & PASS_SEED_V1);
     const GOff G0 = opaque(C.G0);
+    int64_t u[NR];
+    reg_offsets<(int)sizeof(T), NR>(G0, base, u);
     if (!(C.flags & PASS_WIDE)) {
         const uint32_t lane = G0.gt * (uint32_t)sizeof(T);
 #pragma unroll
         for (int i = 0; i < NR; ++i) {
             if (i >= C.nreg) continue;
-            const int64_t u = (base + goff(G0, i)) * (int64_t)sizeof(T);
             if constexpr (NT)
-                v[0][i] = load_stream(reinterpret_cast<const T*>(in0 + u + lane));
+                v[0][i] = load_stream(reinterpret_cast<const T*>(in0 + u[i] + lane));
             else
-                v[0][i] = *reinterpret_cast<const T*>(in0 + u + lane);
+                v[0][i] = *reinterpret_cast<const T*>(in0 + u[i] + lane);
             if constexpr (NV == 2)
-                if (read1) v[1][i] = *reinterpret_cast<const T*>(in1 + u + lane);
+                if (read1) v[1][i] = *reinterpret_cast<const T*>(in1 + u[i] + lane);
         }
     } else {
+        const int64_t lane = (int64_t)G0.gt * (int64_t)sizeof(T);
 #pragma unroll
         for (int i = 0; i < NR; ++i) {
             if (i >= C.nreg) continue;
-            const int64_t e = base + (int64_t)G0.gt + goff(G0, i);
-            v[0][i] = reinterpret_cast<const T*>(in0)[e];
+            v[0][i] = *reinterpret_cast<const T*>(in0 + u[i] + lane);
             if constexpr (NV == 2)
-                if (read1) v[1][i] = reinterpret_cast<const T*>(in1)[e];
+                if (read1) v[1][i] = *reinterpret_cast<const T*>(in1 + u[i] + lane);
         }
     }
 }
@@ -633,26 +639,27 @@ __device__ __forceinline__ void store_tile(const KArgs& a, const PassCtx& C, int
     char* out1 = reinterpret_cast<char*>(a.dst1);
     const bool write0 = !(C.flags & PASS_SKIP_V0);
     const GOff Gl = opaque(C.Gl);
+    int64_t u[NR];
+    reg_offsets<(int)sizeof(T), NR>(Gl, base, u);
     if (!(C.flags & PASS_WIDE)) {
         const uint32_t lane = Gl.gt * (uint32_t)sizeof(T);
 #pragma unroll
         for (int i = 0; i < NR; ++i) {
             if (i >= C.nreg) continue;
-            const int64_t u = (base + goff(Gl, i)) * (int64_t)sizeof(T);
             if constexpr (NT) {
-                if (write0) store_stream(reinterpret_cast<T*>(out0 + u + lane), v[0][i]);
+                if (write0) store_stream(reinterpret_cast<T*>(out0 + u[i] + lane), v[0][i]);
             } else {
-                if (write0) *reinterpret_cast<T*>(out0 + u + lane) = v[0][i];
+                if (write0) *reinterpret_cast<T*>(out0 + u[i] + lane) = v[0][i];
             }
-            if constexpr (NV == 2) *reinterpret_cast<T*>(out1 + u + lane) = v[1][i];
+            if constexpr (NV == 2) *reinterpret_cast<T*>(out1 + u[i] + lane) = v[1][i];
         }
     } else {
+        const int64_t lane = (int64_t)Gl.gt * (int64_t)sizeof(T);
 #pragma unroll
         for (int i = 0; i < NR; ++i) {
             if (i >= C.nreg) continue;
-            const int64_t e = base + (int64_t)Gl.gt + goff(Gl, i);
-            if (write0) reinterpret_cast<T*>(out0)[e] = v[0][i];
-            if constexpr (NV == 2) reinterpret_cast<T*>(out1)[e] = v[1][i];
+            if (write0) *reinterpret_cast<T*>(out0 + u[i] + lane) = v[0][i];
+            if constexpr (NV == 2) *reinterpret_cast<T*>(out1 + u[i] + lane) = v[1][i];
         }
     }
 }
@@ -865,7 +872,7 @@ __device__ __forceinline__ void run_tiles_ph(const KArgs& a, const PK_CONST Pass
                                              int64_t chunk) {
     using T = typename Cplx<R>::T;
     constexpr int NR = 1 << RB;
-    PassCtx C = make_ctx<KMAX, RB>(P);
+    PassCtx C = make_ctx<(int)sizeof(R) * 2, KMAX, RB>(P);
     if constexpr (FULL) {
         C.active = true;
         C.nreg = NR;
@@ -920,18 +927,25 @@ __device__ __forceinline__ void run_tiles_ph(const KArgs& a, const PK_CONST Pass
             int64_t jb = ja;
             const int64_t tb = next(ta, jb);
             const int64_t tbc = tb < ntiles ? tb : ta;
-            const int64_t baseb = base_of(tbc);
-            const TileRefs<R> ub = refs_of(tbc);
-            if (FULL || tb < ntiles) load_tile<R, 1, NR, NT>(a, C, baseb, vb);
+            int64_t baseb = 0;
+            TileRefs<R> ub{(R)1, (R)0};
+            if (FULL || tb < ntiles) {
+                baseb = base_of(tbc);
+                ub = refs_of(tbc);
+                load_tile<R, 1, NR, NT>(a, C, baseb, vb);
+            }
             compute_tile<R, 1, KMAX, RB, FULL>(a, P, C, ta, va, ua, lds, red);
             store_tile<R, 1, NR, NT>(a, C, basea, va);
             if (tb >= ntiles) break;
             int64_t jc = jb;
             const int64_t tc = next(tb, jc);
             const int64_t tcc = tc < ntiles ? tc : tb;
-            const int64_t basec = base_of(tcc);
-            ua = refs_of(tcc);
-            if (FULL || tc < ntiles) load_tile<R, 1, NR, NT>(a, C, basec, va);
+            int64_t basec = 0;
+            if (FULL || tc < ntiles) {
+                basec = base_of(tcc);
+                ua = refs_of(tcc);
+                load_tile<R, 1, NR, NT>(a, C, basec, va);
+            }
             compute_tile<R, 1, KMAX, RB, FULL>(a, P, C, tb, vb, ub, lds, red);
             store_tile<R, 1, NR, NT>(a, C, baseb, vb);
             if (tc >= ntiles) break;
