@@ -196,7 +196,8 @@ enum PassFlags : int32_t {
     PASS_WIDE = 32,    // a thread's byte offset inside a tile may exceed 32 bits
     PASS_STREAM = 64,  // loads and stores are nontemporal (streaming): the last forward pass of
                        // an FP64 instance far larger than the memory-side cache, when it
-                       // writes the tile back in the layout it read
+                       // writes the tile back in the layout it read; in the device's record
+                       // also the passes of states about as large as the L2s
     PASS_LAMBDA = 128, // backward: lambda alone (a one-vector pass), psi is not needed any more
 };
 
