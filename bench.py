@@ -240,7 +240,7 @@ def load_tuning():
 
 
 def batched_run(torch, pk, W, autotune, steps, warmup, prec, insts, record=None, loop=True):
-    """The 4096-instance batch (Sec. 6.2) in one persistent graph-replayed launch, at
+    """The 4096-instance batch (Sec. 6.2) in one persistent launch, at
     the recorded setting (or retuned when ``record`` is None), against a loop of
     single-instance evaluations of the same instances."""
     probs = [{"nq": i["nq"], "gates": i["gates"], "marked": i["marked"]} for i in insts]
@@ -697,7 +697,7 @@ def main():
         log("generated %d batched instances in %.1fs" % (len(insts), time.perf_counter() - t0))
         records = load_tuning()
         line["batched"] = {"workload": "%d noisy Grover instances, n_q = 10..19 log-uniform, seed %d, one "
-                                       "persistent graph-replayed launch" % (len(insts), W.SEEDS["batched"])}
+                                       "persistent launch" % (len(insts), W.SEEDS["batched"])}
         new_records = {}
         for p in ("fp64", "fp32"):
             rec = None if args.retune else records.get("batched_" + p)

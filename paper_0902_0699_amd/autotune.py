@@ -12,7 +12,7 @@ plan on the caller's own buffers. A candidate is:
 * resident workgroups per CU;
 * the team size and threshold of the batched launch.
 
-Timing uses HIP events around a few graph replays. ``tune`` keeps the fastest
+Timing uses HIP events around a few calls. ``tune`` keeps the fastest
 setting, leaves it applied to the plan, and returns it with the table of
 timings.
 

@@ -82,8 +82,9 @@ struct Tiling {
 // log2 of the page size the per-CU address translation cache works in (2 MiB).
 constexpr int kPageByteBit = 21;
 
-// Default tile and register bits per precision, the fastest settings measured
-// for the n_q = 30 Grover iteration: FP64 tiles of 2^13 amplitudes with 16 per
+// Tile and register bits per precision of batches, and of one instance where its size
+// and gates call for no others (choose_tiling); the fastest settings measured for the
+// n_q = 30 Grover iteration: FP64 tiles of 2^13 amplitudes with 16 per
 // thread (2^9 threads); FP32 tiles of 2^13 with 32 per thread (2^8 threads) -- the
 // 2^14 FP32 tile with 16 per thread needs 1024 threads, whose 128-register cap
 // spills the register tile.
@@ -98,8 +99,9 @@ inline int default_page_cap(int prec) { return prec == PK_FP64 ? 4 : 0; }
 // team_size; a team runs the passes of its large instances together, with a
 // barrier between passes, so that an instance too large for one workgroup is
 // still spread over many CUs.  An instance is large when its first pass has at
-// least min_team_tiles * team_size tiles.  Every other instance is taken whole
-// by one workgroup from a queue.  team_size 0 turns teams off.  The device-scope
+// least min_team_tiles * team_size tiles.  Of the others, one larger than half an even
+// share is spread over every workgroup, a pass a launch; the rest are taken whole by
+// one workgroup from a queue.  team_size 0 turns teams off.  The device-scope
 // fences of a team barrier cost more than a single workgroup's sweep of an
 // instance of up to ~2^20 amplitudes, hence the high default threshold.
 struct BatchConfig {
