@@ -240,8 +240,8 @@ def load_tuning():
 
 
 def batched_run(torch, pk, W, autotune, steps, warmup, prec, insts, record=None, loop=True):
-    """The 4096-instance batch (Sec. 6.2) in one persistent launch, at
-    the recorded setting (or retuned when ``record`` is None), against a loop of
+    """The 4096-instance batch (Sec. 6.2) in one call, at the
+    recorded setting (or retuned when ``record`` is None), against a loop of
     single-instance evaluations of the same instances."""
     probs = [{"nq": i["nq"], "gates": i["gates"], "marked": i["marked"]} for i in insts]
     plan = pk.Plan(probs, prec=prec)
@@ -578,7 +578,7 @@ def search_run(torch, pk, W, autotune, reps):
                             "mean_pass_GBs": 32.0 * (1 << nq) * passes / (ms * 1e-3) / 1e9,
                             "L": float(L.item()), "L_closed_form": math.sin((2 * nt + 1) * theta) ** 2}
         log("search n_q=%d: %d iterations, %d passes, %.2f ms, L = %.12f" % (nq, nt, passes, ms, L.item()))
-        # the labelled variant through 2|s><s| - I: one pass per iteration, not the paper's form
+        # the labelled variant through 2|s><s| - I: two sums rotated n_t times, not the paper's form
         pk.search_diffusion(nq, [x], nt, s, out=y)
         torch.cuda.synchronize()
         e0.record()
@@ -588,10 +588,10 @@ def search_run(torch, pk, W, autotune, reps):
         torch.cuda.synchronize()
         msd = e0.elapsed_time(e1) / reps
         out["nq%d" % nq]["diffusion_variant"] = {
-            "method": "(2|s><s| - I) . Oracle, one pass per iteration (not the paper's HALL form)",
+            "method": "(2|s><s| - I) . Oracle, the iterations as one rotation of two sums (not the paper's HALL form)",
             "ms": msd, "iterations_per_s": nt / (msd * 1e-3),
-            "pass_GBs": 2.0 * (1 << nq) * 16 * nt / (msd * 1e-3) / 1e9, "L": float(Ld.item())}
-        log("search n_q=%d, diffusion variant: %.2f ms, L = %.12f" % (nq, msd, Ld.item()))
+            "sweeps_GBs": 3.0 * (1 << nq) * 16 / (msd * 1e-3) / 1e9, "L": float(Ld.item())}
+        log("search n_q=%d, diffusion variant: %.4f ms, L = %.12f" % (nq, msd, Ld.item()))
         del s, y
     return out
 
@@ -697,7 +697,7 @@ def main():
         log("generated %d batched instances in %.1fs" % (len(insts), time.perf_counter() - t0))
         records = load_tuning()
         line["batched"] = {"workload": "%d noisy Grover instances, n_q = 10..19 log-uniform, seed %d, one "
-                                       "persistent launch" % (len(insts), W.SEEDS["batched"])}
+                                       "call" % (len(insts), W.SEEDS["batched"])}
         new_records = {}
         for p in ("fp64", "fp32"):
             rec = None if args.retune else records.get("batched_" + p)
