@@ -213,3 +213,44 @@ def test_batch_with_spread_instances(prec, sizes, tile, team):
             # FP32 norm partials: terms whose rounding the two kernels may contract differently
             ntol = tol + (2.0 ** -22 if prec == "fp32" else 0.0)
             assert not want_norm or abs(norm[i].item() - n1.item()) <= ntol * n1.item()
+
+
+# Passes of one instance about as large as the L2s read and write past the caches' normal
+# replacement: FP64 without 4x4 gates at n_q = 17..20, FP32 with them at 20..22, and
+# lambda's own backward passes; one size outside on each side.
+@pytest.mark.parametrize("nq,prec,pairs,tile", [(16, "fp64", False, None), (17, "fp64", False, None),
+                                                (17, "fp64", False, 7), (20, "fp64", False, None),
+                                                (21, "fp64", False, None), (19, "fp32", True, None),
+                                                (20, "fp32", True, None), (22, "fp32", True, None)])
+def test_streamed_passes_of_small_states(nq, prec, pairs, tile):
+    """Two evaluations in place one after the other, then the gradient of L, against the
+    oracle: each to the precision's bar on a state (1e-12, 1e-5), the gradient to 1e-10
+    (FP64) and 1e-5 (FP32) of its norm."""
+    pk = _pk()
+    rng = np.random.default_rng(nq)
+    marked = sorted(int(v) for v in rng.choice(1 << nq, 8, replace=False))
+    if pairs:
+        gates = []
+        for q in (*range(1, nq, 2), *range(2, nq, 2)):
+            u, _ = np.linalg.qr(rng.standard_normal((4, 4)) + 1j * rng.standard_normal((4, 4)))
+            gates.append(("TWOOP", q, q + 1, u))
+    else:
+        gates = W.grover_gates((3, 4, 0.4, 0.9, 0.2))
+    dt = torch.complex128 if prec == "fp64" else torch.complex64
+    plan = pk.Plan({"nq": nq, "gates": gates, "marked": marked}, prec=prec)
+    if tile:
+        plan.set_tiling(tile, 4)
+    print("streamed n_q=%d tile %s %s" % (nq, tile, prec), flush=True)
+    psi = _state(nq, 7)
+    want, Lw, _ = O.evaluate(nq, gates, marked, O.evaluate(nq, gates, marked, psi)[0])
+    x = torch.from_numpy(psi).to(dt).to("cuda")
+    pk.evaluate(plan, x, out=x)
+    out, L, norm = pk.evaluate(plan, x, out=x)
+    tol = 1e-12 if prec == "fp64" else 1e-5
+    assert np.linalg.norm(out.cpu().to(torch.complex128).numpy() - want) <= tol
+    assert abs(L.item() - Lw) <= tol and abs(norm.item() - 1.0) <= tol
+    once, _, _ = pk.evaluate(plan, torch.from_numpy(psi).to(dt).to("cuda"))
+    gpsi, _ = pk.backward(plan, once, torch.tensor([0.75], dtype=torch.float64, device="cuda"))
+    wpsi, _ = O.adjoint_grad(nq, gates, marked, psi, 0.75)
+    gtol = 1e-10 if prec == "fp64" else 1e-5
+    assert np.linalg.norm(gpsi.cpu().to(torch.complex128).numpy() - wpsi) <= gtol * np.linalg.norm(wpsi)
