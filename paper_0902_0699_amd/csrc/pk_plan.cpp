@@ -567,6 +567,8 @@ struct LocalPass {
     std::vector<std::vector<int>> maps;  // local bit -> state bit; maps[0] when read, back() when written
 };
 
+using CutCache = std::map<std::string, std::vector<int>>;
+
 struct Compiler {
     Plan* plan;
     Instance* in;
@@ -575,7 +577,7 @@ struct Compiler {
     int RBITS;  // register bits of the kernel instance (RB may be smaller for tiny tiles)
     // cut decisions depend only on the structure (nq, tiling, item kinds and bits,
     // what is done); instances of a batch often share it
-    std::map<std::string, std::vector<int>>* cut_cache = nullptr;
+    CutCache* cut_cache = nullptr;
     // the large-stride tile-bit preference of this compile (Tiling::page_cap, or 0
     // where that preference would cost passes)
     int pcap = 0;
@@ -911,16 +913,25 @@ struct Compiler {
         });
     }
 
-    // Passes the tile and cut choices make for `items` with large-stride preference p.
-    int count_passes(const std::vector<ScanItem>& items, int p) {
+    // Passes the tile and cut choices make for `items` with large-stride preference p,
+    // and the LDS exchanges between their stages.
+    int count_passes(const std::vector<ScanItem>& items, int p, int* exchanges = nullptr) {
         const int saved = pcap;
         pcap = p;
         std::vector<char> done(items.size(), 0);
         int left = (int)items.size(), passes = 0;
+        if (exchanges) *exchanges = 0;
         while (left > 0) {
             std::vector<int> sel;
             std::vector<int> t = choose_tile(items, done, &sel);
             sel = choose_cut(items, done, left, t, sel);
+            if (exchanges) {
+                if (plan->tiling.lane_order == 1) order_lanes(&t);
+                const LocalPass lp = local_pass(items, t, sel, sel.size());
+                const int stages = (int)plan_stages(lp.items).size();
+                // a relabelled tile is written from a second stage (see compile)
+                *exchanges += (lp.maps.size() > 1 ? std::max(stages, 2) : stages) - 1;
+            }
             for (int i : sel) done[i] = 1;
             left -= (int)sel.size();
             ++passes;
@@ -1191,13 +1202,20 @@ Prim mat4_prim(Plan* plan, int nq, int is1, int is2, const double* m, Prim::GKin
 const double kSwap4[32] = {1, 0, 0, 0, 0, 0, 0, 0,  0, 0, 0, 0, 1, 0, 0, 0,
                            0, 0, 1, 0, 0, 0, 0, 0,  0, 0, 0, 0, 0, 0, 1, 0};
 
-// Forward passes of a single-instance plan with tiles of 2^tile amplitudes and rb
-// register bits.
-int forward_passes(Plan* plan, int tile, int rb) {
+// A choice of the tiling looks at this many gates of a list (a Fourier transform of 30
+// qubits has 480), so that it costs a long one little next to its compilation.
+constexpr size_t kChoiceGates = 512;
+
+// The forward schedule of a single-instance plan with tiles of 2^tile amplitudes and rb
+// register bits (of a list longer than kChoiceGates: of its beginning).
+struct Outline {
+    int passes, exchanges;
+};
+
+Outline outline(Plan* plan, int tile, int rb, CutCache* cuts, bool want_exchanges = false) {
     Instance& in = plan->inst[0];
-    std::map<std::string, std::vector<int>> cuts;
     Compiler c;
-    c.cut_cache = &cuts;
+    c.cut_cache = cuts;
     c.plan = plan;
     c.in = &in;
     c.backward = false;
@@ -1205,9 +1223,14 @@ int forward_passes(Plan* plan, int tile, int rb) {
     c.C = std::min(plan->tiling.carrier_bits, c.k);
     c.RBITS = rb;
     c.RB = std::min(rb, c.k);
-    const std::vector<ScanItem> items = c.items_of(in.prims);
-    const int cap = plan->tiling.page_cap, n = c.count_passes(items, cap);
-    return cap > 0 ? std::min(n, c.count_passes(items, 0)) : n;
+    std::vector<ScanItem> items = c.items_of(in.prims);
+    if (items.size() > kChoiceGates) items.resize(kChoiceGates);
+    const int cap = plan->tiling.page_cap;
+    Outline o{0, 0}, q{0, 0};
+    o.passes = c.count_passes(items, cap, want_exchanges ? &o.exchanges : nullptr);
+    if (cap <= 0) return o;
+    q.passes = c.count_passes(items, 0, want_exchanges ? &q.exchanges : nullptr);
+    return q.passes < o.passes ? q : o;
 }
 
 std::string fmt(const char* f, long long a = 0, long long b = 0) {
@@ -1218,7 +1241,8 @@ std::string fmt(const char* f, long long a = 0, long long b = 0) {
 
 }  // namespace
 
-static void choose_tiling(Plan* plan);
+static void choose_tiling(Plan* plan, CutCache* cuts);
+static int recompile_with(Plan* plan, std::string* err, CutCache* forward_cuts);
 
 int compile_plan(Plan* plan, const pk_problem* probs, int n_inst, int prec, std::string* err) {
     if (prec != PK_FP64 && prec != PK_FP32) {
@@ -1419,74 +1443,115 @@ int compile_plan(Plan* plan, const pk_problem* probs, int n_inst, int prec, std:
     }
     plan->n_d2 = d2;
     plan->total_elems = off;
-    choose_tiling(plan);
-    return recompile(plan, err);
+    CutCache cuts;  // the compilation takes over what the choice decided for its tiling
+    choose_tiling(plan, &cuts);
+    return recompile_with(plan, err, &cuts);
 }
 
 // Tile and register bits of a single-instance plan that the caller leaves to the
 // library.  A tile of 2^13 amplitudes (128 KB in FP64) takes a CU's LDS and so most
-// of its time moves one tile after the other; it pays where it saves passes.  Measured
-// per call (us), G a noisy Grover iteration, Q the Fourier transform of 2/3 of the
-// qubits, T a two-qubit gate on every neighbouring pair; kX/rY: tiles of 2^X, Y
-// register bits:
+// of its time moves one tile after the other; it pays where it saves passes, and where
+// HBM alone bounds them.  Measured per call (us), G a noisy Grover iteration, + its
+// additions, H a Hadamard on every qubit, QF r the Fourier transform of r qubits, T a
+// two-qubit gate on every neighbouring pair; X/Y: tiles of 2^X, Y register bits:
 //  * up to 2^20 amplitudes the state gives few tiles, and smaller ones with 8
 //    amplitudes a thread (more, shorter waves) shorten every step of the one chain of
-//    latencies that a workgroup then is.  FP64 (13/4 -> chosen): G 9 15.8 -> 12.8,
-//    G 16 32.5 -> 24.9, G 18 38.9 -> 30.5, G 20 55.8 -> 49.0 (k12/r4), Q 18 39.1 ->
-//    31.6.  FP32 (13/5 ->): G 12 21.2 -> 13.5, G 16 34.6 -> 23.4, Q 20 82.5 -> 42.9.
-//    4x4 steps keep 16 amplitudes a thread, which hold two qubit pairs a stage: FP64
-//    T 16 49.5 -> 35.8, FP32 T 16 55.8 -> 37.1, T 20 78.1 -> 61.8.
-//  * above, 2^12 tiles leave two workgroups a CU, which hide each other's latencies,
-//    but more passes cost more than that: FP64 G 24 495 -> 451, G 27 4276 -> 4435
-//    (HBM-bound, equal passes); Q 24 439 -> 400, Q 26 (one pass more) 1708 -> 2074,
-//    Q 30 40290 -> 34819 (k12/r3); T 24 644 -> 613, T 27 (one more) 4789 -> 4616.
-//    FP32 phases take twice as long with 32 amplitudes a thread (Q 28: 13/5 9654,
-//    k12/r4 5107).
-static void choose_tiling(Plan* plan) {
+//    latencies that a workgroup then is.  FP64 (13/4 -> chosen): G 16 30.8 -> 24.5,
+//    G 18 36.9 -> 28.8, G 20 42.9 -> 39.2 (12/4), QF 20 87.6 -> 78.9.  FP32 (13/5 ->):
+//    G 16 34.4 -> 23.7, QF 20 178.8 -> 61.6.  4x4 steps keep 16 amplitudes a thread,
+//    which hold two qubit pairs a stage: T 16 FP64 42.5 -> 32.6, FP32 50.5 -> 33.5.
+//    At 2^19 and 2^20 that is worth half as many passes more (QF 13 of 20 qubits, 2
+//    passes 51.4, 3 passes 12/3 45.9), not twice as many (QF 9 of 19 26.8 and 29.5).
+//  * 2^21 and 2^22: a pass more costs more than smaller tiles give (FP64 G 21 + one phase
+//    60.0, 5 passes of 12/3 84.8; H + 12 phases 22 78.1 and 93.5); at equal passes 12/3
+//    is the faster (QF 14 of 21 68.6 and 62.7, QF 22 200 and 186).
+//  * 2^23 and 2^24, up to the memory-side cache's 256 MB in FP64: 2^12 tiles leave two
+//    workgroups a CU, which hide each other's latencies (FP64 G 24 514 and 481, T 24 489
+//    and 465, QF 24 706 and 695).
+//  * above, HBM bounds a pass of few gates, and 2^13 is the faster (FP64 G 25 1038 and
+//    1078, G + one phase 26 2124 and 2208, G + one D4 28 8849 and 9639); passes that are
+//    dense in phases or 4x4 steps gain from the second workgroup as before (H + 12
+//    phases 25 .. 28 732 and 665, 1434 and 1367, 2730 and 2638, 5666 and 5143, T 30 39373
+//    and 38925; the line: G + 16 phases 25 .. 28 1208 and 1145, 2335 and 2367, 4452 and
+//    4562, 9376 and 9222, H + 6 phases 26 1229 and 1296).  A quarter as many phases, an
+//    eighth as many 4x4 steps as other gates are taken as dense.  A pass more
+//    costs all of it (T 25, 4 passes for 3, 1023 and 1069; QF + CNOT 30, 7 for 6, 62755
+//    and 65385).
+//  * FP32 tiles take half the LDS, so 2^12 pays longer: to 2^27 with any phase (G + one
+//    phase 23 149 and 141, 27 2261 and 2159) and with 4x4 steps even for a pass more (T
+//    25 710 and 626, 27 2846 and 2627), not at 2^28 (G + 8 CNOT, 6 for 5, 5458 and 6076).
+//    2^13 tiles there have 32 amplitudes a thread (G + one phase 29 10744 with 16, 9052
+//    with 32), except where phases outnumber the other gates three to one, which take
+//    twice as long with 32 (QF 14 of 28 4850 and 6015; 3 to 1: even).  n_q = 22 with 4x4
+//    steps keeps 16, two qubit pairs a stage, although 32 measured the faster there (87
+//    and 72, G + one D4).
+static void choose_tiling(Plan* plan, CutCache* cuts) {
     Tiling& t = plan->tiling;
     if (plan->inst.size() != 1 || !t.automatic) return;
     const Instance& in = plan->inst[0];
-    const int nq = in.nq, big = default_tile_bits(plan->prec), rb0 = default_reg_bits(plan->prec);
+    const int nq = in.nq, big = default_tile_bits(plan->prec);
     const bool fp64 = plan->prec == PK_FP64;
-    bool mat4 = false, phase = false;
+    int ones = 0, phases = 0, fours = 0;
     for (const Prim& p : in.prims) {
-        phase = phase || (p.kind == Prim::GATE && p.gk == Prim::GPHASE);
-        mat4 = mat4 || (p.kind == Prim::GATE && p.bit2 >= 0 && p.gk != Prim::GPHASE && p.gk != Prim::GSWAP);
+        if (p.kind != Prim::GATE || p.gk == Prim::GSWAP) continue;
+        if (p.gk == Prim::GPHASE)
+            ++phases;
+        else if (p.bit2 >= 0)
+            ++fours;
+        else
+            ++ones;
     }
+    auto passes = [&](int tile, int rb) { return outline(plan, tile, rb, cuts).passes; };
     if (nq <= 12) {
-        t.reg_bits = mat4 ? 4 : 3;
+        t.reg_bits = fours ? 4 : 3;
     } else if (nq == 13) {
-        // one 2^13 tile, or eight of 2^10: FP64 G 22.8 and 22.2, T 36.1 and 27.1; FP32 G 19.7
-        // (r4) and 21.5
-        const bool one = !fp64 && !mat4 && !phase;
+        // one 2^13 tile, or eight of 2^10: FP64 G 21.8 and 22.2, G + 2 CNOT 24.2 and 26.5, + 8
+        // 33.5 and 32.8, T 31.0 and 27.4; FP32 G 19.5 and 21, G + one phase 20.4 and 22.1, QF
+        // 39 and 37, G + 8 CNOT 29 and 33.5, T even
+        const bool one = fp64 ? fours && 4 * fours < ones : fours || !phases;
         t.tile_bits = one ? big : 10;
-        t.reg_bits = one || mat4 ? 4 : 3;
+        t.reg_bits = one || fours ? 4 : 3;
     } else if (nq <= 20) {
         // the smallest tile that takes no more passes (two tiles with 4 common bits cover
         // the state from (nq + 4) / 2 on)
         int k = std::max(10, (nq + 5) / 2);
-        if (mat4 || phase) {
-            const bool more = nq > 18 && !mat4;  // 2^12 tiles even for a pass more
-            const int most = more ? 1 << 30 : forward_passes(plan, big, mat4 ? 4 : rb0);
-            if (more) k = 12;
-            while (k < big && forward_passes(plan, k, mat4 ? 4 : 3) > most) ++k;
+        if (fours || phases) {
+            int most = passes(big, fours ? 4 : default_reg_bits(plan->prec));
+            if (nq > 18 && !fours) {
+                k = 12;
+                most = most * 3 / 2;
+            }
+            while (k < big && passes(k, fours ? 4 : 3) > most) ++k;
         }
         t.tile_bits = k;
-        t.reg_bits = mat4 || (fp64 && k >= 12 && !phase) ? 4 : 3;
-    } else if (phase && !mat4 && fp64) {
-        const bool small = nq <= 22 || forward_passes(plan, 12, 4) <= forward_passes(plan, big, 4);
+        t.reg_bits = fours || (fp64 && k >= 12 && !phases) ? 4 : 3;
+    } else {
+        const bool dense4 = fours > 0 && 8 * fours >= ones, dense = dense4 || (phases > 0 && 4 * phases >= ones);
+        const bool most_phases = phases >= 3 * std::max(1, ones);
+        bool small = false;
+        if (fours || phases || (fp64 && (nq == 23 || nq == 24))) {
+            const int rb12 = fp64 && nq <= 22 && !fours ? 3 : 4, more = passes(12, rb12) - passes(big, 4);
+            if (nq <= 22)
+                small = more <= 0 && (fours ? dense4 || (!fp64 && most_phases) : fp64 || nq == 21 || most_phases);
+            else if (fp64)
+                small = more < 0 || (more == 0 && (nq <= 24 || dense));
+            else if (nq <= 27)
+                small = more <= (fours ? 1 : 0);
+            else
+                small = more < 0 || (more == 0 && dense);
+        }
         t.tile_bits = small ? 12 : big;
-        t.reg_bits = small && (nq <= 22 || nq >= 27) ? 3 : 4;
-    } else if (phase && !mat4) {
-        t.reg_bits = 4;
-        if (forward_passes(plan, 12, 4) <= forward_passes(plan, big, 4)) t.tile_bits = 12;
-    } else if (mat4) {
-        t.reg_bits = 4;
-        if (forward_passes(plan, 12, 4) <= forward_passes(plan, big, 4) + (nq >= 23 ? 1 : 0)) t.tile_bits = 12;
-    } else if (fp64) {
-        if (nq >= 23 && nq <= 25 && forward_passes(plan, 12, 4) <= forward_passes(plan, big, 4)) t.tile_bits = 12;
-    } else if (nq == 21) {
-        t.reg_bits = 4;
+        t.reg_bits = fp64 || small || nq == 21 || (nq == 22 && fours) || most_phases ? 4 : 5;
+        // 2^12 FP64 tiles with phases take 8 amplitudes a thread to 2^22 (QF 22 207 with 16,
+        // 186), and from 2^27 where that takes at most a quarter more LDS exchanges: QF 10 of 27 .. 30
+        // (equal) 2351 and 2151, 4984 and 4334, 10566 and 9136, 19166 and 17560, QF 20 (5 for
+        // 4) 4282 and 4321, 8719 and 8669, 18470 and 17675, 35276 and 34428; QF 14 (3 for 2)
+        // 3080 and 3119, 6025 and 6266, QF 8 (2 for 1) 9380 and 11330.  Between, 16 are as
+        // fast or faster (QF 6 of 25 and 26, equal, 258 and 263, 478 and 500)
+        if (fp64 && small && phases && !fours &&
+            (nq <= 22 || (nq >= 27 && 4 * outline(plan, 12, 3, cuts, true).exchanges <=
+                                          5 * outline(plan, 12, 4, cuts, true).exchanges)))
+            t.reg_bits = 3;
     }
 }
 
@@ -1531,7 +1596,11 @@ static bool streams_small(const Plan* plan, int nq, const HostPass& hp) {
 }
 
 int recompile(Plan* plan, std::string* err) {
-    (void)err;
+    CutCache cuts;
+    return recompile_with(plan, err, &cuts);
+}
+
+static int recompile_with(Plan* plan, std::string* err, CutCache* forward_cuts) {
     plan->passes.clear();
     plan->stages.clear();
     plan->flips.clear();
@@ -1551,11 +1620,11 @@ int recompile(Plan* plan, std::string* err) {
     }
     plan->n_reads = read_base;
 
+    CutCache backward_cuts;
     for (int dir = 0; dir < 2; ++dir) {
-        std::map<std::string, std::vector<int>> cut_cache;
         for (auto& in : plan->inst) {
             Compiler c;
-            c.cut_cache = &cut_cache;
+            c.cut_cache = dir == 0 ? forward_cuts : &backward_cuts;
             c.plan = plan;
             c.in = &in;
             c.backward = dir == 1;

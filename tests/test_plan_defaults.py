@@ -68,3 +68,52 @@ def test_automatic_settings_stay_within_the_kernels(nq, prec, kind):
     plan.set_launch(0, 0)
     d = plan.describe()
     assert d["tile_bits"] == 13 and {p["rbits"] for p in d["instances"][0]["forward"]} == {default}
+
+
+def _mixed(kind, nq):
+    """A Grover iteration with a few gates of another kind, or a list dense in them."""
+    g = W.grover_gates((2, 2, 0.7, 0.4, 0.0))
+    rng = np.random.default_rng(nq)
+    u, _ = np.linalg.qr(rng.standard_normal((4, 4)) + 1j * rng.standard_normal((4, 4)))
+    return {"one_phase": g + [("CPHASEK", 1, nq, 3)], "phase_inside": g[:3] + [("CPHASE", nq // 2, nq // 2 + 1)] + g[3:],
+            "one_cnot": g + [("CNOT", 1, nq // 2)], "one_d4": g + [("D4", 2, nq - 2, 0.1, 0.2, 0.3)],
+            "phases": W.phase_circuit(rng, nq, 12), "qft_half": [("QFT", 1, nq // 2)], "qft": [("QFT", 1, nq)],
+            "brickwork": [("TWOOP", q, q + 1, u) for first in (1, 2) for q in range(first, nq, 2)],
+            "qft_cnot": [("QFT", 1, nq), ("CNOT", 1, 2)]}[kind]
+
+
+@pytest.mark.parametrize("kind", ["one_phase", "phase_inside", "one_cnot", "one_d4", "phases", "qft_half", "qft",
+                                  "brickwork", "qft_cnot"])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("nq", [14, 18, 19, 20, 21, 22, 23, 24, 25, 26, 27, 28, 29, 30])
+def test_automatic_tiles_cost_no_passes(nq, prec, kind):
+    """The chosen tiles take no more passes than 2^13 ones, but for half as many more at
+    2^19 and 2^20 amplitudes with phases, and one more in FP32 from 2^23 to 2^27 with 4x4
+    steps."""
+    gates = _mixed(kind, nq)
+    fours = kind in ("one_cnot", "one_d4", "brickwork", "qft_cnot")
+    auto = pk.Plan({"nq": nq, "gates": gates, "marked": [1]}, prec=prec)
+    big = pk.Plan({"nq": nq, "gates": gates, "marked": [1]}, prec=prec)
+    big.set_launch(0, 4 if fours or prec == "fp64" else 5)
+    big.set_tiling(13, 4)
+    most = big.passes()
+    if nq in (19, 20) and not fours:
+        most = most * 3 // 2
+    if prec == "fp32" and 23 <= nq <= 27 and fours:
+        most += 1
+    assert auto.passes() <= most
+
+
+def test_automatic_registers_follow_the_share_of_phases():
+    """FP32 2^13 tiles: 32 amplitudes a thread with few phases, 16 where most gates are;
+    FP64 2^12 tiles from 2^27 on: 8 where that takes at most a quarter more exchanges than 16."""
+    def rbits(nq, prec, gates):
+        d = pk.Plan({"nq": nq, "gates": gates, "marked": []}, prec=prec).describe()
+        return d["tile_bits"], {p["rbits"] for p in d["instances"][0]["forward"]}
+    assert rbits(29, "fp32", _mixed("one_phase", 29)) == (13, {5})
+    assert rbits(29, "fp32", _mixed("phases", 29)) == (13, {5})
+    assert rbits(28, "fp32", _mixed("qft", 28)) == (13, {4})
+    assert rbits(28, "fp64", [("QFT", 1, 8)]) == (12, {4})
+    assert rbits(28, "fp64", [("QFT", 1, 10)]) == (12, {3})
+    assert rbits(28, "fp64", [("QFT", 1, 14)]) == (12, {4})
+    assert rbits(28, "fp64", [("QFT", 1, 20)]) == (12, {3})
