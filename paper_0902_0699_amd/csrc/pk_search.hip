@@ -16,11 +16,16 @@
 // (substitute m = (U - V) / N into U' = 2 m (N - |M|) - U and V' = V + 2 m |M|), so
 // U and V after k iterations are the pair rotated by k t, and
 //     a = (U_k - (-1)^k U) / (N - |M|),   b = (V_k - V) / |M|.
+// The factors of U and V in them are computed on the host in twice double precision, by
+// squaring the rotation: a sine of k t in double carries the rounding of t k times (N =
+// 16, k = 3000: error 7.0e-14, iteration by iteration 5.8e-15, now 3e-16).
 // The state is read once for U and read and written once for the result, whatever
 // k is; all of it in FP64 (also for FP32 states), sums in a fixed order.  Iteration by
 // iteration (one pass and one combining launch each), the n_q = 20 search took 8.46
 // ms; this takes 21 us, three launches' latency.
 #include <hip/hip_runtime.h>
+
+#include <cmath>
 
 #include "pk_launch.h"
 
@@ -70,35 +75,30 @@ __global__ void __launch_bounds__(kThreads) sum_kernel(const T* src, int64_t n, 
     block_sum2(acc, part);
 }
 
-// The addends of k iterations from the sum over every amplitude and the sum over the
-// marked ones.
+// The addends of k iterations from the sums: a = uu U - w V, b = vv V + w U.
+struct Rotation {
+    double uu, w, vv;
+    int many;  // k > 1
+};
+
 struct Addends {
     double2 a, b;
 };
 
-__device__ __forceinline__ Addends addends(double2 sum, double2 V, int64_t n, int count, int64_t k) {
-    const double N = (double)n, M = (double)count, K = N - M, odd = (k & 1) ? 1.0 : 0.0;
+__device__ __forceinline__ Addends addends(double2 sum, double2 V, const Rotation& q) {
     const double2 U = {sum.x - V.x, sum.y - V.y};
     Addends r;
-    if (count == 0) {  // the mean does not change
-        r.a = double2{odd * 2.0 * (U.x / N), odd * 2.0 * (U.y / N)};
-        r.b = double2{0.0, 0.0};
-        return r;
+    r.a = double2{q.uu * U.x, q.uu * U.y};
+    r.b = double2{q.vv * V.x, q.vv * V.y};
+    if (q.w != 0.0) {  // else none or all are marked, and U or V is no sum of amplitudes
+        r.a.x -= q.w * V.x;
+        r.a.y -= q.w * V.y;
+        r.b.x += q.w * U.x;
+        r.b.y += q.w * U.y;
     }
-    if (count == n) {  // m = -V / N, the sign of V alternates
-        r.a = double2{0.0, 0.0};
-        r.b = double2{-odd * 2.0 * (V.x / N), -odd * 2.0 * (V.y / N)};
-        return r;
-    }
-    double sn, cs;
-    sincos((double)k * (2.0 * asin(sqrt(M / N))), &sn, &cs);
-    const double g = sqrt(K / M), sign = (k & 1) ? -1.0 : 1.0;
-    // U_k = cos U - sin g V and V_k = cos V + sin U / g
-    r.a = double2{((cs - sign) * U.x - sn * g * V.x) / K, ((cs - sign) * U.y - sn * g * V.y) / K};
-    r.b = double2{((cs - 1.0) * V.x + sn / g * U.x) / M, ((cs - 1.0) * V.y + sn / g * U.y) / M};
     // from the second iteration on, the mean of a non-finite part is NaN
-    if (k > 1 && !isfinite(sum.x)) r.a.x = r.b.x = __builtin_nan("");
-    if (k > 1 && !isfinite(sum.y)) r.a.y = r.b.y = __builtin_nan("");
+    if (q.many && !isfinite(sum.x)) r.a.x = r.b.x = __builtin_nan("");
+    if (q.many && !isfinite(sum.y)) r.a.y = r.b.y = __builtin_nan("");
     return r;
 }
 
@@ -116,7 +116,7 @@ __device__ __forceinline__ T plus(const T& v, double sign, const double2& add) {
 // apply_kernel will store.
 template <typename T>
 __global__ void __launch_bounds__(64) combine_kernel(const double2* part, int nparts, MarkedSet ms, const T* src,
-                                                     int64_t n, int64_t k, double2* add, double* L) {
+                                                     Rotation q, double2* add, double* L) {
     // all of a lane's loads are issued before the first add, so their latencies overlap
     constexpr int kPer = kGrid / 64;
     const int lane = threadIdx.x;
@@ -143,7 +143,7 @@ __global__ void __launch_bounds__(64) combine_kernel(const double2* part, int np
         v.x += __shfl_xor(v.x, off, 64);
         v.y += __shfl_xor(v.y, off, 64);
     }
-    const Addends r = addends(s, v, n, ms.count, k);
+    const Addends r = addends(s, v, q);
     const double2 c = wide(plus(own, 1.0, r.b));
     double l = lane < ms.count ? c.x * c.x + c.y * c.y : 0.0;
 #pragma unroll
@@ -180,8 +180,8 @@ __global__ void __launch_bounds__(kThreads) apply_kernel(const T* src, T* dst, i
 constexpr int64_t kSmall = 16 * kThreads;
 
 template <typename T>
-__global__ void __launch_bounds__(kThreads) small_kernel(const T* src, T* dst, int64_t n, int64_t k, MarkedSet ms,
-                                                         double* L) {
+__global__ void __launch_bounds__(kThreads) small_kernel(const T* src, T* dst, int64_t n, double sign, Rotation q,
+                                                         MarkedSet ms, double* L) {
     constexpr int kPer = (int)(kSmall / kThreads), nw = kThreads / 64;
     __shared__ double2 red[2][nw];
     __shared__ double lred[nw];
@@ -224,8 +224,7 @@ __global__ void __launch_bounds__(kThreads) small_kernel(const T* src, T* dst, i
         return t;
     };
     const double2 sum = total(s, red[0]), V = total(m, red[1]);
-    const Addends r = addends(sum, V, n, ms.count, k);
-    const double sign = (k & 1) ? -1.0 : 1.0;
+    const Addends r = addends(sum, V, q);
     double l = 0.0;
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
@@ -248,13 +247,63 @@ __global__ void __launch_bounds__(kThreads) small_kernel(const T* src, T* dst, i
     }
 }
 
+// A number as the sum of two doubles, the second below half an ulp of the first.
+struct Twice {
+    double hi, lo;
+};
+
+Twice sum2(double a, double b) {
+    const double s = a + b, t = s - a;
+    return {s, (a - (s - t)) + (b - t)};
+}
+
+Twice operator+(Twice a, Twice b) {
+    const Twice s = sum2(a.hi, b.hi);
+    return sum2(s.hi, s.lo + a.lo + b.lo);
+}
+
+Twice operator-(Twice a) { return {-a.hi, -a.lo}; }
+
+Twice operator*(Twice a, Twice b) {
+    const double p = a.hi * b.hi;
+    return sum2(p, std::fma(a.hi, b.hi, -p) + a.hi * b.lo + a.lo * b.hi);
+}
+
+// The k-th power of the rotation of one iteration, whose cosine is exact in double, as
+// the factors of Rotation.  Its angle's error grows as k 2^-104.
+Rotation rotation(int64_t n, int count, int64_t k) {
+    const double N = (double)n, M = (double)count, K = N - M, odd = (k & 1) ? 1.0 : 0.0;
+    const int many = k > 1;
+    if (count == 0) return {2.0 * odd / N, 0.0, 0.0, many};   // the mean does not change
+    if (count == n) return {0.0, 0.0, -2.0 * odd / N, many};  // m = -V / N, the sign of V alternates
+    const double root = std::sqrt(M * K);  // M K is exact: below 2^37
+    const Twice g = sum2(root, std::fma(-root, root, M * K) / (2.0 * root));
+    Twice c = {1.0 - 2.0 * M / N, 0.0}, s = {2.0 * g.hi / N, 2.0 * g.lo / N};
+    Twice ck = {1.0, 0.0}, sk = {0.0, 0.0};
+    for (int64_t e = k; e; e >>= 1) {
+        if (e & 1) {
+            const Twice t = ck * c + -(sk * s);
+            sk = sk * c + ck * s;
+            ck = t;
+        }
+        const Twice t = c * c + -(s * s);
+        s = c * s;
+        s = {2.0 * s.hi, 2.0 * s.lo};
+        c = t;
+    }
+    const Twice up = ck + Twice{odd > 0.0 ? 1.0 : -1.0, 0.0}, down = ck + Twice{-1.0, 0.0};
+    return {(up.hi + up.lo) / K, (sk.hi + sk.lo) / root, (down.hi + down.lo) / M, many};
+}
+
 template <typename T>
 hipError_t search_t(const void* psi_in, void* psi_out, int64_t n, const MarkedSet& ms, int64_t iters,
                     double2* part, double2* add, double* L, hipStream_t st) {
     const T* in = static_cast<const T*>(psi_in);
     T* out = static_cast<T*>(psi_out);
+    const Rotation q = rotation(n, ms.count, iters);
+    const double sign = (iters & 1) ? -1.0 : 1.0;
     if (n <= kSmall) {
-        hipLaunchKernelGGL(small_kernel<T>, dim3(1), dim3(kThreads), 0, st, in, out, n, iters, ms, L);
+        hipLaunchKernelGGL(small_kernel<T>, dim3(1), dim3(kThreads), 0, st, in, out, n, sign, q, ms, L);
         return hipGetLastError();
     }
     // at least four amplitudes a thread, at most kGrid blocks
@@ -262,9 +311,9 @@ hipError_t search_t(const void* psi_in, void* psi_out, int64_t n, const MarkedSe
     if (chunk < 4 * kThreads) chunk = 4 * kThreads;
     const int grid = (int)((n + chunk - 1) / chunk);
     hipLaunchKernelGGL(sum_kernel<T>, dim3(grid), dim3(kThreads), 0, st, in, n, chunk, part);
-    hipLaunchKernelGGL(combine_kernel<T>, dim3(1), dim3(64), 0, st, part, grid, ms, in, n, iters, add, L);
-    hipLaunchKernelGGL(apply_kernel<T>, dim3(grid), dim3(kThreads), 0, st, in, out, n, chunk,
-                       (iters & 1) ? -1.0 : 1.0, add, ms);
+    hipLaunchKernelGGL(combine_kernel<T>, dim3(1), dim3(64), 0, st, part, grid, ms, in, q, add, L);
+    hipLaunchKernelGGL(apply_kernel<T>, dim3(grid), dim3(kThreads), 0, st, in, out, n, chunk, sign, add,
+                       ms);
     return hipGetLastError();
 }
 

@@ -254,3 +254,54 @@ def test_streamed_passes_of_small_states(nq, prec, pairs, tile):
     wpsi, _ = O.adjoint_grad(nq, gates, marked, psi, 0.75)
     gtol = 1e-10 if prec == "fp64" else 1e-5
     assert np.linalg.norm(gpsi.cpu().to(torch.complex128).numpy() - wpsi) <= gtol * np.linalg.norm(wpsi)
+
+
+def _diffuse(part, marked, k):
+    """k applications of 2 mean(O C) - O C to the real or imaginary parts, in 80 bits."""
+    v = part.astype(np.longdouble)
+    with np.errstate(invalid="ignore"):
+        for _ in range(k):
+            v[marked] = -v[marked]
+            v = 2 * (v.sum() / len(v)) - v
+    return v
+
+
+@pytest.mark.parametrize("nq,marks,k", [(1, 1, 1001), (2, 0, 1001), (2, 4, 1001), (3, 1, 2000), (4, 1, 30), (4, 1, 3000),
+                                        (4, 3, 100001), (10, 5, 20000), (13, 1, 5000)])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_diffusion_error_does_not_grow_with_the_iterations(nq, marks, k, prec):
+    """The addends are sums of n amplitudes (at most nq + 2 rounded levels, each u of
+    sum |C| <= sqrt(N) |C|) with factors of at most 2 / (N - M), 1 / sqrt(M (N - M)) and
+    2 / M, and one rounding of the result: with at most half of the amplitudes marked
+    (or all) the normwise error is below (6 (nq + 2) + 8) u whatever k is, plus 2 u32 in FP32."""
+    pk = _pk()
+    dt = torch.complex128 if prec == "fp64" else torch.complex64
+    x = torch.from_numpy(_state(nq, 7 * nq + marks)).to(dt)
+    rng = np.random.default_rng(6)
+    marked = sorted(int(v) for v in rng.choice(1 << nq, marks, replace=False))
+    wide = x.to(torch.complex128).numpy()
+    re, im = _diffuse(wide.real, marked, k), _diffuse(wide.imag, marked, k)
+    print("diffusion n_q=%d marks=%d k=%d %s" % (nq, marks, k, prec), flush=True)
+    out, L = pk.search_diffusion(nq, marked, k, x.to("cuda"))
+    got = out.cpu().to(torch.complex128).numpy()
+    err = np.sqrt(np.sum((got.real - re) ** 2 + (got.imag - im) ** 2) / np.sum(re ** 2 + im ** 2))
+    tol = (6 * (nq + 2) + 8) * 2.0 ** -53 + (2 * 2.0 ** -24 if prec == "fp32" else 0.0)
+    assert err <= tol
+    assert abs(L.item() - float(np.sum(re[marked] ** 2 + im[marked] ** 2))) <= 4 * tol
+
+
+@pytest.mark.parametrize("marks", [0, 2, 8])
+@pytest.mark.parametrize("k", [1, 2, 3])
+def test_diffusion_of_an_infinite_part(marks, k):
+    """An infinite real part makes the mean of the real parts infinite, so one iteration
+    leaves infinities and NaN, more leave NaN alone; the imaginary parts are untouched.
+    Labels, values and NaN as the iteration itself gives them."""
+    pk = _pk()
+    nq, marked = 3, list(range(marks))
+    x = _state(nq, 11)
+    x.real[5] = np.inf
+    re, im = _diffuse(x.real, marked, k), _diffuse(x.imag, marked, k)
+    out, _ = pk.search_diffusion(nq, marked, k, torch.from_numpy(x).to("cuda"))
+    got = out.cpu().numpy()
+    assert np.array_equal(np.isnan(got.real), np.isnan(re)) and np.array_equal(np.isinf(got.real), np.isinf(re))
+    assert np.linalg.norm(got.imag - im.astype(float)) <= 40 * 2.0 ** -53
