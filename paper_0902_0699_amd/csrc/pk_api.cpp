@@ -267,18 +267,15 @@ hipError_t enqueue_prep(DevPlan* d, PassLaunch* L, void* ws, const double* angle
     return launch_prep(p, st);
 }
 
-// The largest number of tiles whose norm partials the last pass combines itself: up to
-// it, the launch saved (~5 us) costs less than one workgroup's reading them.
-constexpr int64_t kSelfCombine = 4096;
-
-// Has the pass that launches next combine L and the norm of `P` itself, where it may.
-bool self_combine(PassLaunch* L, const Plan& P, double* L_out, double* norm_out) {
-    if (P.inst[0].fwd.back().ntiles > kSelfCombine) return false;
-    L->ticket = at<unsigned int>(P.d_tables, table_layout(&P).ticket);
-    L->L_out = L_out;
-    L->norm_out = norm_out;
-    L->n_reads = (int32_t)P.inst[0].marked.size();
-    return true;
+// Whether the last pass of an evaluation of `launches` passes combines L and the norm
+// itself.  Its workgroups are counted by a ticket in the workspace, which the first pass
+// clears, so that evaluations with workspaces of their own never meet and none leaves
+// anything for the next; a single pass of one workgroup needs no ticket, one of several
+// has nobody to clear it.  Up to 4096 tiles the launch saved (~5 us) costs less than one
+// workgroup's reading their norm partials.
+bool self_combine(const Plan& P, int64_t launches) {
+    const int64_t ntiles = P.inst[0].fwd.back().ntiles;
+    return ntiles == 1 || (launches > 1 && ntiles <= 4096);
 }
 
 // Evaluation of a single-instance plan: prep, every forward pass, final combine.
@@ -291,16 +288,24 @@ hipError_t enqueue_eval(DevPlan* d, const EvalArgs& a, hipStream_t st, std::vect
     PassLaunch L = base_launch(d, a.ws, PK_OP_EVAL);
     hipError_t e = enqueue_prep(d, &L, a.ws, a.angles, PK_OP_EVAL, 0, st);
     if (e != hipSuccess) return e;
-    bool combined = false;
     L.dst0 = a.psi_out;
     L.nv = 1;
     const Instance& in = P.inst[0];
+    const int64_t launches = reps * (int64_t)in.fwd.size();
+    const bool combined = self_combine(P, launches);
+    unsigned int* ticket = at<unsigned int>(a.ws, workspace_layout(&P, PK_OP_EVAL).counters);
     for (int64_t r = 0; r < reps; ++r) {
         L.src0 = r == 0 ? a.psi_in : a.psi_out;
         L.want_norm = a.norm_out != nullptr && r == reps - 1;
         for (size_t p = 0; p < in.fwd.size(); ++p) {
             set_pass(&L, P, in.fwd[p], (int)p);
-            if (r == reps - 1 && p + 1 == in.fwd.size()) combined = self_combine(&L, P, a.L_out, a.norm_out);
+            L.clear = combined && launches > 1 && r == 0 && p == 0 ? ticket : nullptr;
+            if (combined && r == reps - 1 && p + 1 == in.fwd.size()) {
+                L.ticket = ticket;
+                L.L_out = a.L_out;
+                L.norm_out = a.norm_out;
+                L.n_reads = (int32_t)in.marked.size();
+            }
             if (ev) hipEventRecord((*ev)[2 * p], st);
             e = launch_pass(L, st);
             if (ev) hipEventRecord((*ev)[2 * p + 1], st);

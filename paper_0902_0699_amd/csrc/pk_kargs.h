@@ -31,10 +31,11 @@ struct KArgs {
     int32_t stage_begin;  // of this pass (single-instance launches)
     int32_t nstages;
     // set on the last pass of an evaluation that combines its readouts itself (else null)
-    unsigned int* ticket;  // workgroups done; zero before and after
+    unsigned int* ticket;  // counts the workgroups done, in the evaluation's workspace
     double* L_out;
     double* norm_out;      // written when want_norm
     int32_t n_reads;
+    unsigned int* clear;   // set on the first pass of such an evaluation: the ticket it clears
 };
 
 // Sum of one double per thread over the workgroup; result valid in thread 0.

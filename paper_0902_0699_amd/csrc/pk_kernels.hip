@@ -159,6 +159,7 @@ static KArgs kargs(const PassLaunch& L) {
     a.L_out = L.L_out;
     a.norm_out = L.norm_out;
     a.n_reads = L.n_reads;
+    a.clear = L.clear;
     return a;
 }
 

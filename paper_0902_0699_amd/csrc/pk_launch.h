@@ -35,6 +35,7 @@ struct PassLaunch {
     double* L_out;
     double* norm_out;
     int32_t n_reads;
+    unsigned int* clear;   // not null: the pass clears this ticket for a later one
     int64_t grid_cap;  // workgroups per CU of a pass launch; 0 = as many as fit
 };
 

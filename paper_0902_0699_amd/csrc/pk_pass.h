@@ -670,7 +670,9 @@ __device__ __forceinline__ void store_tile(const KArgs& a, const PassCtx& C, int
 }
 
 // Stores a readout or norm partial; where the pass itself combines them (KArgs::ticket)
-// past the caches of this XCD, to where the combining workgroup reads it.
+// past the caches of this XCD, to where the combining workgroup reads it.  Every store to
+// `reads` and `partials` in a single-instance launch goes through here: finish_single
+// orders no others.
 __device__ __forceinline__ void publish(const KArgs& a, double* p, double x) {
     if (a.ticket)
         __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1018,13 +1020,20 @@ __device__ __forceinline__ double combine(const double* src, int64_t count, doub
 }
 
 // L and the norm of a single instance, by the workgroup of its last pass that finishes
-// last (a ticket counts them; it ends at zero, as it started, for the next launch).
-// Every readout and partial was stored past the caches (publish) and has completed
-// when its wave gets here, so no cache is written back or invalidated for it: the
-// fences that would do so cost a grid barrier ~9 us, a combining launch ~5 us.
+// last: a ticket counts them, cleared by the evaluation's first pass (an earlier launch
+// on the stream).  What orders the data before the ticket: agent-scope atomic stores,
+// additions and loads are done at the level of memory that all XCDs share, past their
+// L2s (the sc1 bit; LLVM's AMDGPU memory model for gfx942 and gfx950); the workgroup
+// fence has each wave wait until its stores are done there and keeps the compiler from
+// moving them; the barrier waits for every wave; only then does thread 0 add to the
+// ticket.  The last workgroup's loads depend on what that addition returned, and the
+// second fence keeps them behind it.  An agent-scope release would write back every
+// dirty line of the L2, the whole state: such fences cost a grid barrier ~9 us, a
+// combining launch ~5 us.
 template <int NT>
 __device__ __forceinline__ void finish_single(const KArgs& a, const PK_CONST Pass* P, double* red) {
     __shared__ int last;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (threadIdx.x == 0)
@@ -1032,11 +1041,9 @@ __device__ __forceinline__ void finish_single(const KArgs& a, const PK_CONST Pas
                __hip_atomic_fetch_add(a.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
     __syncthreads();
     if (!last) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
     const double L = combine<NT>(a.reads, a.n_reads, red);
-    if (threadIdx.x == 0) {
-        *a.L_out = L;
-        if (gridDim.x > 1) __hip_atomic_store(a.ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    if (threadIdx.x == 0) *a.L_out = L;
     if (a.want_norm) {
         const double norm = combine<NT>(a.partials + P->part_base, P->ntiles, red);
         if (threadIdx.x == 0) *a.norm_out = norm;
@@ -1068,8 +1075,12 @@ pass_kernel(KArgs a) {
         const int64_t c = walk > 0 ? walk : (ntiles + G - 1) / G;
         run_tiles<R, NV, KMAX, RB, true>(a, P, (int64_t)blockIdx.x * c, G, ntiles, lds, red, c);
     }
-    if constexpr (NV == 1)
-        if (a.ticket) finish_single<(1 << (KMAX - RB))>(a, P, red);
+    if constexpr (NV == 1) {
+        if (a.ticket)
+            finish_single<(1 << (KMAX - RB))>(a, P, red);
+        else if (a.clear && blockIdx.x == 0 && threadIdx.x == 0)
+            *a.clear = 0u;
+    }
 }
 
 // Team barrier of the batched launch: every member adds one to the team's

@@ -1851,8 +1851,6 @@ TableLayout table_layout(const Plan* plan) {
     o = align256(o);
     t.spread_red = o;  // their evaluation reductions
     o = align256(o + 2 * plan->team.spread.size() * sizeof(Reduction));
-    t.ticket = o;  // workgroups done of a last pass that combines its readouts
-    o = align256(o + sizeof(uint32_t));
     t.total = std::max<size_t>(o, 256);
     return t;
 }
@@ -1870,7 +1868,7 @@ WsLayout workspace_layout(const Plan* plan, int op) {
     o = align256(o + (size_t)plan->n_reads * sizeof(double));
     w.gpart = o;
     if (op == PK_OP_BACKWARD) o = align256(o + (size_t)plan->n_gpart * sizeof(double));
-    w.counters = o;  // batched queue, barrier time-out flag, one barrier counter per team
+    w.counters = o;  // batched queue, barrier time-out flag, one barrier counter per team; or a ticket
     o = align256(o + (plan->inst.size() + 8 + kMaxTeams) * sizeof(int64_t));
     w.state = o;
     if (op == PK_OP_BACKWARD) {

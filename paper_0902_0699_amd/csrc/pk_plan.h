@@ -189,7 +189,7 @@ std::string describe(const Plan* plan);
 // Byte offsets of the device table arrays inside plan->d_tables.
 struct TableLayout {
     size_t passes, stages, phases, twid, urefs, mats, mats4, params, idesc, order, team_off, team_list, red, built, built4,
-        ticket, spread, spread_red, total;
+        spread, spread_red, total;
 };
 TableLayout table_layout(const Plan* plan);
 

@@ -305,3 +305,55 @@ def test_diffusion_of_an_infinite_part(marks, k):
     got = out.cpu().numpy()
     assert np.array_equal(np.isnan(got.real), np.isnan(re)) and np.array_equal(np.isinf(got.real), np.isinf(re))
     assert np.linalg.norm(got.imag - im.astype(float)) <= 40 * 2.0 ** -53
+
+
+@pytest.mark.parametrize("nq,tile,gates,angles", [(13, None, None, False), (16, None, None, False), (16, 6, None, True),
+                                                  (18, None, None, True), (15, 10, [("H", 3)], False),
+                                                  (9, None, [("H", 3)], False)])
+def test_overlapping_evaluations_of_one_plan(nq, tile, gates, angles):
+    """Evaluations on two streams, each with its own buffers and a workspace that starts as
+    arbitrary bytes, share nothing that one of them writes: every L and norm of either
+    equals that of one evaluation alone bit for bit.  Plans of one and of several passes and
+    tiles."""
+    pk = _pk()
+    lib, reps = pk.lib(), 60
+    plan = pk.Plan({"nq": nq, "gates": gates or W.grover_gates((1, 3, 0.5, 0.8, 0.0)), "marked": [1, 6]})
+    if tile:
+        plan.set_tiling(tile, 3)
+    print("overlapping evaluations n_q=%d tile %s angles %s" % (nq, tile, angles), flush=True)
+    ang = [torch.tensor([0.5, 0.8, 0.1 * i], dtype=torch.float64, device="cuda") if angles else None for i in range(2)]
+    x = [torch.from_numpy(_state(nq, i)).to("cuda") for i in range(2)]
+    alone = [pk.evaluate(plan, x[i], angles=ang[i]) for i in range(2)]
+    y = [torch.empty_like(x[0]) for _ in range(2)]
+    out = [torch.zeros((reps, 2), dtype=torch.float64, device="cuda") for _ in range(2)]
+    ws = [torch.full((plan.workspace_bytes(pk.PK_OP_EVAL),), 255, dtype=torch.uint8, device="cuda") for _ in range(2)]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    for r in range(reps):
+        for i in range(2):
+            o = out[i][r].data_ptr()
+            rc = lib.pk_evaluate(plan.handle, x[i].data_ptr(), y[i].data_ptr(), o, o + 8,
+                                 ang[i].data_ptr() if angles else None, ws[i].data_ptr(), streams[i].cuda_stream)
+            assert rc == 0
+    torch.cuda.synchronize()
+    for i in range(2):
+        assert torch.equal(y[i], alone[i][0])
+        assert torch.equal(out[i], torch.stack([alone[i][1], alone[i][2]], 1).expand(reps, 2))
+
+
+def test_repeated_one_pass_list_combines_once():
+    """A list of one pass over several tiles: alone, its readouts take a launch of their
+    own; repeated, the first application clears the ticket of the last.  U^3 against three
+    evaluations, from a workspace of arbitrary bytes."""
+    pk = _pk()
+    nq = 15
+    plan = pk.Plan({"nq": nq, "gates": [("ONEOP", 3, np.array([[0.6, 0.8j], [0.8j, 0.6]]))], "marked": [4, 77]})
+    plan.set_tiling(10, 4)
+    assert plan.passes() == 1
+    x = torch.from_numpy(_state(nq, 2)).to("cuda")
+    plan.workspace(pk.PK_OP_EVAL, x.device).fill_(255)
+    got = pk.evaluate_repeat(plan, x, 3)
+    want = x
+    for _ in range(3):
+        want, L, norm = pk.evaluate(plan, want)
+    assert torch.equal(got[0], want) and torch.equal(got[1], L) and torch.equal(got[2], norm)
