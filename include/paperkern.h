@@ -235,7 +235,9 @@ int pk_plan_passes(const pk_plan* plan, int32_t inst, int32_t* passes);
 
 /*
  * pk_plan_describe -- JSON text of the compiled schedule (passes, tile bits,
- * stages and their gate lists).  Writes at most `cap` bytes including the NUL;
+ * stages and their gate lists).  A pass's `walk` and `overlap` are the caller's
+ * settings (0 where there are none); an instance's `used` lists, pass by pass, the
+ * walk, the overlapped loop and the streaming that run.  Writes at most `cap` bytes including the NUL;
  * *needed receives the full size.  Host-only; for tests and tools.
  */
 int pk_plan_describe(const pk_plan* plan, char* buf, int64_t cap, int64_t* needed);

@@ -106,7 +106,7 @@ def tune_backward_walk(plan, psi_out, dL, angles=None, reps=2, walks=WALKS):
     Returns (walk, {walk: ms})."""
     import torch
     d = plan.describe()["instances"][0]
-    fwd = [p["walk"] for p in d["forward"]]
+    fwd = [p["walk"] for p in d["used"]["forward"]]
     nb = len(d["backward"])
     times = {}
     for w in walks:

@@ -2029,7 +2029,18 @@ std::string describe(const Plan* plan) {
             }
             s += "]";
         }
-        s += "}";
+        // what the passes run with: the caller's settings or the library's choice
+        size_t first[2] = {(size_t)plan->idesc[i].first_pass, (size_t)plan->n_fwd_passes};
+        for (size_t j = 0; j < i; ++j) first[1] += plan->inst[j].bwd.size();
+        for (int dir = 0; dir < 2; ++dir) {
+            s += dir == 0 ? ",\"used\":{\"forward\":[" : "],\"backward\":[";
+            for (size_t p = 0; p < (dir == 0 ? in.fwd : in.bwd).size(); ++p) {
+                const Pass& u = plan->passes[first[dir] + p];
+                s += (p ? "," : "") + std::string("{\"walk\":") + std::to_string(u.walk) + ",\"overlap\":" +
+                     std::to_string(u.overlap) + ",\"stream\":" + std::to_string((u.flags & PASS_STREAM) ? 1 : 0) + "}";
+            }
+        }
+        s += "]}}";
     }
     s += "],\"phases\":[";
     for (size_t q = 0; q < plan->phases.size(); ++q) {

@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 
 import oracle as O
+from paper_0902_0699_amd import autotune as AT
 from paper_0902_0699_amd import paperkern as pk
 from paper_0902_0699_amd import workload as W
 from schedule_emulator import run_backward, run_forward
@@ -117,3 +118,53 @@ def test_automatic_registers_follow_the_share_of_phases():
     assert rbits(28, "fp64", [("QFT", 1, 10)]) == (12, {3})
     assert rbits(28, "fp64", [("QFT", 1, 14)]) == (12, {4})
     assert rbits(28, "fp64", [("QFT", 1, 20)]) == (12, {3})
+
+
+def _used(plan):
+    return plan.describe()["instances"][0]["used"]
+
+
+def test_describe_reports_what_the_passes_use():
+    """The library's overlapped loop and streaming where the caller set nothing, else the
+    caller's settings; a batch's instances use neither."""
+    prob = {"nq": 24, "gates": W.phase_circuit(np.random.default_rng(1), 24, 12), "marked": [1]}
+    plan = pk.Plan(prob)
+    n, nb = plan.passes(), len(_used(plan)["backward"])
+    assert any(p["overlap"] == 1 for p in _used(plan)["forward"])
+    assert all(p["overlap"] == 0 for p in plan.describe()["instances"][0]["forward"])
+    plan.set_pass_overlap([0] * n)
+    plan.set_pass_walk([4] * n + [16] * nb)
+    assert all(p["overlap"] == 0 and p["walk"] == 4 for p in _used(plan)["forward"])
+    assert all(p["walk"] == 16 for p in _used(plan)["backward"])
+    big = pk.Plan({"nq": 30, "gates": W.grover_gates((2, 2, 0.4, 0.1, 0.2)), "marked": [1]})
+    assert [p["stream"] for p in _used(big)["forward"]] == [0] * (big.passes() - 1) + [1]
+    batch = pk.Plan([prob, dict(prob, nq=24)])
+    for inst in batch.describe()["instances"]:
+        assert all(p == {"walk": 0, "overlap": 0, "stream": 0} for p in inst["used"]["forward"] + inst["used"]["backward"])
+
+
+class _NoTimer:
+    def __init__(self, **_):
+        pass
+
+    def record(self):
+        pass
+
+    def elapsed_time(self, _):
+        return 1.0
+
+
+@pytest.mark.parametrize("walks", [None, 16])
+def test_backward_walk_tuning_keeps_the_forward(walks, monkeypatch):
+    """tune_backward_walk leaves the forward passes' walk and loop as they were, set by the
+    caller or not (no kernel runs: the timing is replaced)."""
+    import torch
+    monkeypatch.setattr(torch.cuda, "Event", _NoTimer)
+    monkeypatch.setattr(torch.cuda, "synchronize", lambda: None)
+    monkeypatch.setattr(pk, "backward", lambda *a, **k: None)
+    plan = pk.Plan({"nq": 30, "gates": W.grover_gates((2, 2, 0.4, 0.1, 0.2)), "marked": [1]})
+    if walks:
+        plan.set_pass_walk([walks] * plan.passes())
+    before = _used(plan)["forward"]
+    AT.tune_backward_walk(plan, None, None)
+    assert _used(plan)["forward"] == before
