@@ -94,7 +94,7 @@ def tune_walk(plan, psi_in, psi_out, reps=3, walks=WALKS, overlap=True):
             pk.time_passes(plan, psi_in, psi_out)
             times[(w, ov)] = np.median(np.array([pk.time_passes(plan, psi_in, psi_out) for _ in range(reps)]), axis=0)
     best = [min(times, key=lambda c: times[c][p]) for p in range(n)]
-    plan.set_pass_overlap([c[1] for c in best] if len(modes) > 1 else [])
+    plan.set_pass_overlap([c[1] for c in best])
     plan.set_pass_walk([c[0] for c in best])
     named = {("%d+o" % w if ov else str(w)): [float(v) for v in t] for (w, ov), t in times.items()}
     return [c[0] for c in best], named

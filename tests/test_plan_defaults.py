@@ -168,3 +168,17 @@ def test_backward_walk_tuning_keeps_the_forward(walks, monkeypatch):
     before = _used(plan)["forward"]
     AT.tune_backward_walk(plan, None, None)
     assert _used(plan)["forward"] == before
+
+
+@pytest.mark.parametrize("overlap", [True, False])
+def test_walk_tuning_applies_a_loop_it_timed(overlap, monkeypatch):
+    """tune_walk leaves every pass with a walk and a loop of the combinations that it timed:
+    without `overlap` the plain loop, also where the library would overlap (the timing is
+    replaced by one that favours the last combination)."""
+    calls = []
+    monkeypatch.setattr(pk, "time_passes", lambda plan, *_: calls.append(_used(plan)["forward"]) or
+                        [100.0 - len(calls)] * plan.passes())
+    plan = pk.Plan({"nq": 24, "gates": W.phase_circuit(np.random.default_rng(1), 24, 12), "marked": [1]})
+    AT.tune_walk(plan, None, None, reps=1, walks=(0, 2), overlap=overlap)
+    got = _used(plan)["forward"]
+    assert got in calls and all(p["overlap"] == int(overlap) and p["walk"] == 2 for p in got)
