@@ -3,7 +3,8 @@
 The best tile for a workload depends on the memory system's response to the
 pass's access pattern and on the kernel's register and LDS footprint, which are
 measured, not modelled. ``tune`` therefore times every candidate setting of a
-plan on the caller's own buffers. A candidate is:
+plan on the caller's own buffers, the tile and register bits the plan comes with (the
+library's choice, until they are set) among them. A candidate is:
 
 * tile bits;
 * carrier bits;
@@ -64,6 +65,18 @@ def apply(plan, cfg):
     plan.set_tiling(cfg["tile_bits"], cfg["carrier_bits"], 1, cfg["lane_order"], cfg.get("page_cap", -1))
     plan.set_launch(cfg["wgs_per_cu"], cfg["reg_bits"])
     plan.set_batch(cfg.get("team_size", 16), cfg.get("min_team_tiles", 64))
+
+
+def current(plan, op="eval"):
+    """The plan's tile, carrier and register bits as a candidate, with the defaults of the
+    rest, or None where ``op`` has no such kernel.  A tile that the library chose is one
+    that the setters can ask for, so applying this again gives the same schedule."""
+    d = plan.describe()
+    rb = d["instances"][0]["forward"][0]["rbits"]
+    if op == "batched" and rb == 3:
+        return None
+    return {"tile_bits": d["tile_bits"], "carrier_bits": d["carrier_bits"], "lane_order": 1, "reg_bits": rb,
+            "wgs_per_cu": 0, "team_size": 16, "min_team_tiles": 64}
 
 
 WALKS = (0, 2, 4, 16, 64, -1)
@@ -197,8 +210,9 @@ def _time(torch, run, reps, warmup):
 
 
 def tune(plan, run, op="eval", reps=3, warmup=1, cands=None, use_cache=True):
-    """Times ``run()`` (one evaluation with ``plan``) under every candidate setting;
-    applies and returns (best setting, [(setting, ms), ...]) sorted by time."""
+    """Times ``run()`` (one evaluation with ``plan``) under every candidate setting (without
+    ``cands``: ``candidates`` and the plan's current one); applies and returns (best
+    setting, [(setting, ms), ...]) sorted by time."""
     import torch
 
     key = "%s|%s" % (_device_name(torch), signature(plan, op))
@@ -209,7 +223,12 @@ def tune(plan, run, op="eval", reps=3, warmup=1, cands=None, use_cache=True):
             apply(plan, hit["best"])
             return hit["best"], [(c, ms) for c, ms in hit["table"]]
     table = []
-    for cfg in (cands if cands is not None else candidates(plan.prec, op)):
+    if cands is None:
+        cands = candidates(plan.prec, op)
+        own = current(plan, op)
+        if own and own not in cands:
+            cands.insert(0, own)
+    for cfg in cands:
         try:
             apply(plan, cfg)
         except pk.PaperkernError:

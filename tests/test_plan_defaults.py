@@ -182,3 +182,17 @@ def test_walk_tuning_applies_a_loop_it_timed(overlap, monkeypatch):
     AT.tune_walk(plan, None, None, reps=1, walks=(0, 2), overlap=overlap)
     got = _used(plan)["forward"]
     assert got in calls and all(p["overlap"] == int(overlap) and p["walk"] == 2 for p in got)
+
+
+@pytest.mark.parametrize("nq,prec", [(12, "fp64"), (14, "fp64"), (16, "fp32"), (18, "fp32"), (20, "fp64"), (24, "fp64")])
+def test_tuning_can_keep_the_automatic_setting(nq, prec, monkeypatch):
+    """The setting that the library chose is among those that tune times, and applying it
+    gives the same schedule back (the timing is replaced by one that favours it)."""
+    plan = pk.Plan({"nq": nq, "gates": W.grover_gates((2, 2, 0.4, 0.1, 0.2)), "marked": [1]}, prec=prec)
+    own = plan.describe()["instances"]
+    monkeypatch.setattr(AT, "_time", lambda *_: 1.0 if plan.describe()["instances"] == own else 2.0)
+    best, table = AT.tune(plan, None, use_cache=False)
+    assert plan.describe()["instances"] == own and table[0][1] == 1.0 and table[-1][1] == 2.0
+    monkeypatch.setattr(AT, "_time", lambda *_: 1.0 if plan.describe()["instances"] != own else 2.0)
+    AT.tune(plan, None, use_cache=False, cands=[dict(best, tile_bits=11, reg_bits=4)])
+    assert plan.describe()["tile_bits"] == 11
