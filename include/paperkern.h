@@ -164,9 +164,8 @@ int pk_set_launch(pk_plan* plan, int32_t wgs_per_cu, int32_t reg_bits);
  * pk_set_pass_walk -- the order in which a single-instance plan's passes hand
  * tiles to workgroups: one entry per forward pass (n = pk_plan_passes), or one
  * per forward pass followed by one per backward pass (pk_backward); n = 0
- * leaves the choice to the library (by precision and tile count; 0 in most
- * passes), as before the first call.  Over a grid of G workgroups,
- * workgroup w takes: 0, tiles w, w + G, ... (the workgroups
+ * resets every pass to 0.  Over a grid of G workgroups,
+ * workgroup w takes: 0, tiles w, w + G, ... (the default: the workgroups
  * resident at once cover neighbouring tiles); c in 2..65536, runs of c
  * consecutive tiles starting at tiles w c, (w + G) c, ...; -1, one contiguous
  * block of ceil(ntiles / G) tiles.  Results do not change; which walk is faster

@@ -1555,19 +1555,11 @@ static void choose_tiling(Plan* plan, CutCache* cuts) {
     }
 }
 
-// The tile walk of a pass that the caller leaves to the library.  At n_q = 30 (2^17
-// tiles) runs of two take the five passes of an FP64 iteration from 34.1 to 33.4 ms and
-// the Fourier transform from 40.3 to 39.2; with fewer tiles no walk is the faster one
-// (n_q = 29: 16.8 strided, 17.5 runs of two; n_q = 27: 4.31, 4.26).
-static int32_t default_walk(const Plan* plan, const HostPass& hp) {
-    return plan->prec == PK_FP64 && hp.k == 13 && hp.ntiles >= (int64_t)1 << 17 ? 2 : 0;
-}
-
-// The overlapped tile loop of such a pass: where there are exchanges to overlap and at
-// least four tiles a workgroup (it reads one tile more than it works on).  FP64, 2^13
-// tiles, default and overlapped loop (us): n_q = 22 109 and 113, 23 280 and 266, 26 2198
-// and 2114, 30 34.1 and 33.4 ms; a streamed pass of 2^16 tiles or more loses (n_q = 29
-// 3158 and 3299).  At 2^12 tiles two workgroups a CU overlap anyway: Hadamard passes
+// The overlapped tile loop of a pass that the caller leaves to the library: where there
+// are exchanges to overlap and at least four tiles a workgroup (it reads one tile more
+// than it works on).  FP64, 2^13 tiles, default and overlapped loop (us): n_q = 22 109 and
+// 113, 23 280 and 266, 26 2198 and 2114, 30 34.1 and 33.4 ms; a streamed pass of 2^16
+// tiles or more loses (n_q = 29 3158 and 3299).  At 2^12 tiles two workgroups a CU overlap anyway: Hadamard passes
 // lose (n_q = 24 451 and 461) below 2^14 tiles, passes with phases or 4x4 steps gain
 // (416 and 400, 628 and 613; FP32 489 and 467).
 static int32_t default_overlap(const Plan* plan, const HostPass& hp) {
@@ -1717,7 +1709,7 @@ static int recompile_with(Plan* plan, std::string* err, CutCache* forward_cuts) 
             emit(plan->inst[i], (int)i, hp);
             if (plan->inst.size() != 1) continue;
             if (streams_small(plan, plan->inst[i].nq, hp)) plan->passes.back().flags |= PASS_STREAM;
-            plan->passes.back().walk = plan->walk.empty() ? default_walk(plan, hp) : plan->walk[p];
+            plan->passes.back().walk = plan->walk.empty() ? 0 : plan->walk[p];
             plan->passes.back().overlap = plan->overlap.empty() ? default_overlap(plan, hp) : plan->overlap[p];
         }
     plan->n_fwd_passes = (int)plan->passes.size();

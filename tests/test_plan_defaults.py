@@ -196,3 +196,14 @@ def test_tuning_can_keep_the_automatic_setting(nq, prec, monkeypatch):
     monkeypatch.setattr(AT, "_time", lambda *_: 1.0 if plan.describe()["instances"] != own else 2.0)
     AT.tune(plan, None, use_cache=False, cands=[dict(best, tile_bits=11, reg_bits=4)])
     assert plan.describe()["tile_bits"] == 11
+
+
+@pytest.mark.parametrize("nq,prec", [(12, "fp64"), (24, "fp64"), (29, "fp64"), (30, "fp64"), (31, "fp32")])
+def test_automatic_walk_is_strided(nq, prec):
+    """No size has a tile walk of its own: strided until the caller sets one, and again
+    after an empty list."""
+    plan = pk.Plan({"nq": nq, "gates": W.grover_gates((2, 2, 0.4, 0.1, 0.2)), "marked": [1]}, prec=prec)
+    for _ in range(2):
+        assert all(p["walk"] == 0 for p in _used(plan)["forward"] + _used(plan)["backward"])
+        plan.set_pass_walk([64] * plan.passes())
+        plan.set_pass_walk([])
