@@ -1202,6 +1202,24 @@ Prim mat4_prim(Plan* plan, int nq, int is1, int is2, const double* m, Prim::GKin
 const double kSwap4[32] = {1, 0, 0, 0, 0, 0, 0, 0,  0, 0, 0, 0, 1, 0, 0, 0,
                            0, 0, 1, 0, 0, 0, 0, 0,  0, 0, 0, 0, 0, 0, 1, 0};
 
+// What an instance's list holds, SWAPs apart: one-qubit gates, phases, 4x4 steps.
+struct GateMix {
+    int ones = 0, phases = 0, fours = 0;
+    // lists whose passes compute enough to hide under it what HBM alone would bound
+    // (measured at choose_tiling)
+    bool dense4() const { return fours > 0 && 8 * fours >= ones; }
+    bool dense() const { return dense4() || (phases > 0 && 4 * phases >= ones); }
+};
+
+GateMix gate_mix(const Instance& in) {
+    GateMix m;
+    for (const Prim& p : in.prims) {
+        if (p.kind != Prim::GATE || p.gk == Prim::GSWAP) continue;
+        ++(p.gk == Prim::GPHASE ? m.phases : p.bit2 >= 0 ? m.fours : m.ones);
+    }
+    return m;
+}
+
 // A choice of the tiling looks at this many gates of a list (a Fourier transform of 30
 // qubits has 480), so that it costs a long one little next to its compilation.
 constexpr size_t kChoiceGates = 512;
@@ -1491,16 +1509,8 @@ static void choose_tiling(Plan* plan, CutCache* cuts) {
     const Instance& in = plan->inst[0];
     const int nq = in.nq, big = default_tile_bits(plan->prec);
     const bool fp64 = plan->prec == PK_FP64;
-    int ones = 0, phases = 0, fours = 0;
-    for (const Prim& p : in.prims) {
-        if (p.kind != Prim::GATE || p.gk == Prim::GSWAP) continue;
-        if (p.gk == Prim::GPHASE)
-            ++phases;
-        else if (p.bit2 >= 0)
-            ++fours;
-        else
-            ++ones;
-    }
+    const GateMix mix = gate_mix(in);
+    const int ones = mix.ones, phases = mix.phases, fours = mix.fours;
     auto passes = [&](int tile, int rb) { return outline(plan, tile, rb, cuts).passes; };
     if (nq <= 12) {
         t.reg_bits = fours ? 4 : 3;
@@ -1526,19 +1536,18 @@ static void choose_tiling(Plan* plan, CutCache* cuts) {
         t.tile_bits = k;
         t.reg_bits = fours || (fp64 && k >= 12 && !phases) ? 4 : 3;
     } else {
-        const bool dense4 = fours > 0 && 8 * fours >= ones, dense = dense4 || (phases > 0 && 4 * phases >= ones);
         const bool most_phases = phases >= 3 * std::max(1, ones);
         bool small = false;
         if (fours || phases || (fp64 && (nq == 23 || nq == 24))) {
             const int rb12 = fp64 && nq <= 22 && !fours ? 3 : 4, more = passes(12, rb12) - passes(big, 4);
             if (nq <= 22)
-                small = more <= 0 && (fours ? dense4 || (!fp64 && most_phases) : fp64 || nq == 21 || most_phases);
+                small = more <= 0 && (fours ? mix.dense4() || (!fp64 && most_phases) : fp64 || nq == 21 || most_phases);
             else if (fp64)
-                small = more < 0 || (more == 0 && (nq <= 24 || dense));
+                small = more < 0 || (more == 0 && (nq <= 24 || mix.dense()));
             else if (nq <= 27)
                 small = more <= (fours ? 1 : 0);
             else
-                small = more < 0 || (more == 0 && dense);
+                small = more < 0 || (more == 0 && mix.dense());
         }
         t.tile_bits = small ? 12 : big;
         t.reg_bits = fp64 || small || nq == 21 || (nq == 22 && fours) || most_phases ? 4 : 5;
@@ -1555,21 +1564,30 @@ static void choose_tiling(Plan* plan, CutCache* cuts) {
     }
 }
 
-// The overlapped tile loop of a pass that the caller leaves to the library: where there
-// are exchanges to overlap and at least four tiles a workgroup (it reads one tile more
-// than it works on).  FP64, 2^13 tiles, default and overlapped loop (us): n_q = 22 109 and
-// 113, 23 280 and 266, 26 2198 and 2114, 30 34.1 and 33.4 ms; a streamed pass of 2^16
-// tiles or more loses (n_q = 29 3158 and 3299).  At 2^12 tiles two workgroups a CU overlap anyway: Hadamard passes
-// lose (n_q = 24 451 and 461) below 2^14 tiles, passes with phases or 4x4 steps gain
-// (416 and 400, 628 and 613; FP32 489 and 467).
-static int32_t default_overlap(const Plan* plan, const HostPass& hp) {
-    if (hp.rbits != 4 || hp.stages.size() < 2 || hp.ntiles < 1024 || hp.k < 12) return 0;
+// The overlapped tile loop of a pass that the caller leaves to the library: with 16
+// amplitudes a thread, tiles of 2^12 or more and at least four tiles a workgroup (it reads
+// one tile more than it works on).  Measured over whole evaluations (us), every pass plain
+// and every pass overlapped:
+//  * 2^13 tiles, one workgroup a CU: FP64 G 22 102 and 107, 23 270 and 263, 27 4643 and
+//    4386, QF 16 of 25 863 and 810, T 28 10220 and 9256; FP32 QF 18 of 27 3535 and 3110.
+//    A streamed pass of 2^16 tiles or more loses (n_q = 30 5957 and 6174).
+//  * 2^12 tiles, two workgroups a CU that overlap anyway: Hadamard passes lose (FP64 G 24
+//    483 and 490, 28 8641 and 8907), lists dense in phases or 4x4 steps gain in every pass
+//    (FP64 QF 15 of 23 208 and 200, H + 12 phases 25 724 and 689, T 22 138 and 133; FP32 QF
+//    16 of 24 238 and 220), phases in FP64 from 2^11 tiles on (QF 14 of 22 FP64 112 and
+//    119, FP32 90 and 85).  Plain and overlapped passes mixed are slower than either while the state fits the caches (QF 15
+//    of 23 225, H + 12 phases 23 165, 166 and 178), so only from 2^13 tiles on does a list
+//    with a few such steps overlap the passes that hold them (FP32 G + one phase 25 511 and
+//    491, FP64 1101 and 1089).
+static int32_t default_overlap(bool fp64, const GateMix& mix, const HostPass& hp) {
+    if (hp.rbits != 4 || hp.ntiles < 1024 || hp.k < 12) return 0;
     if (hp.flags & PASS_STREAM) return hp.ntiles < (1 << 16);
+    if (hp.k == 13) return 1;
+    if (hp.k == 12 && (mix.dense4() || (mix.dense() && hp.ntiles >= (fp64 ? 2048 : 1024)))) return 1;
     bool heavy = !hp.phases.empty();
     for (const HostStage& hs : hp.stages)
         for (const Op& o : hs.ops) heavy = heavy || o.kind == OP_MAT4;
-    if (plan->prec != PK_FP64) return heavy;
-    return heavy || hp.k == 13 || hp.ntiles >= (1 << 14);
+    return heavy && hp.ntiles >= 8192;
 }
 
 // Whether a one-vector pass of a small state streams (the device's PASS_STREAM): a
@@ -1700,6 +1718,7 @@ static int recompile_with(Plan* plan, std::string* err, CutCache* forward_cuts) 
         }
         plan->passes.push_back(p);
     };
+    const GateMix mix = gate_mix(plan->inst[0]);
     for (size_t i = 0; i < plan->inst.size(); ++i)
         for (size_t p = 0; p < plan->inst[i].fwd.size(); ++p) {
             HostPass& hp = plan->inst[i].fwd[p];
@@ -1710,7 +1729,7 @@ static int recompile_with(Plan* plan, std::string* err, CutCache* forward_cuts) 
             if (plan->inst.size() != 1) continue;
             if (streams_small(plan, plan->inst[i].nq, hp)) plan->passes.back().flags |= PASS_STREAM;
             plan->passes.back().walk = plan->walk.empty() ? 0 : plan->walk[p];
-            plan->passes.back().overlap = plan->overlap.empty() ? default_overlap(plan, hp) : plan->overlap[p];
+            plan->passes.back().overlap = plan->overlap.empty() ? default_overlap(plan->prec == PK_FP64, mix, hp) : plan->overlap[p];
         }
     plan->n_fwd_passes = (int)plan->passes.size();
     for (size_t i = 0; i < plan->inst.size(); ++i)
