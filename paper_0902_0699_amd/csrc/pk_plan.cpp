@@ -1575,9 +1575,9 @@ static void choose_tiling(Plan* plan, CutCache* cuts) {
 //    483 and 490, 28 8641 and 8907), lists dense in phases or 4x4 steps gain in every pass
 //    (FP64 QF 15 of 23 208 and 200, H + 12 phases 25 724 and 689, T 22 138 and 133; FP32 QF
 //    16 of 24 238 and 220), phases in FP64 from 2^11 tiles on (QF 14 of 22 FP64 112 and
-//    119, FP32 90 and 85).  Plain and overlapped passes mixed are slower than either while the state fits the caches (QF 15
-//    of 23 225, H + 12 phases 23 165, 166 and 178), so only from 2^13 tiles on does a list
-//    with a few such steps overlap the passes that hold them (FP32 G + one phase 25 511 and
+//    119, FP32 90 and 85).  Plain and overlapped passes mixed are slower than either while
+//    the state fits the caches (QF 15 of 23 225, H + 12 phases 23 165, 166 and 178), so only
+//    from 2^13 tiles on does a list with a few such steps overlap the passes that hold them (FP32 G + one phase 25 511 and
 //    491, FP64 1101 and 1089).
 static int32_t default_overlap(bool fp64, const GateMix& mix, const HostPass& hp) {
     if (hp.rbits != 4 || hp.ntiles < 1024 || hp.k < 12) return 0;
@@ -1591,18 +1591,17 @@ static int32_t default_overlap(bool fp64, const GateMix& mix, const HostPass& hp
 }
 
 // Whether a one-vector pass of a small state streams (the device's PASS_STREAM): a
-// pass ends with the write-back of every dirty line of the L2s, which a state of their
-// size makes long; stores that stream leave less of it.  Measured with and without
-// (us): FP64 without 4x4 steps, n_q = 20 (16 MiB) 48.7 -> 39.7 an iteration, 17 26.4 ->
-// 25.4, 18 30.6 -> 29.2, 19 even, 21 57.6 -> 58.7; with 4x4 steps n_q = 20 64.7 -> 66.5;
-// FP32 with them n_q = 20 56.8 -> 53.1, 22 103.5 -> 92.0, without 20 38.5 -> 39.1.
+// pass ends with the write-back of every dirty line of the L2s (32 MB in all), which a
+// state of half their size, read from one buffer and written to another, fills; stores
+// that stream leave less of it.  Without and with (us), lists as at choose_tiling: 16 MiB,
+// FP64 G 20 49.6 and 42.1, G + one CNOT 56.2 and 47.1, T 58.5 and 59.5; FP32 G 21 56.1 and
+// 51.1, T 60.0 and 53.9.  32 MiB FP32 G 22 65.8 and 64.1, T 100.5 and 89.6, but FP64 G 21
+// 59.4 and 60.2; 64 MiB FP64 G 22 101 and 105, FP32 G 23 144 and 155.  Below, FP64 G 17
+// 26.4 and 26.0, 18 30.6 and 30.0, 19 36.3 and 37.0, T 17 34.1 and 33.5; FP32 G 18 27.8 and
+// 29.5, 20 37.7 and 39.0, T 20 52.2 and 49.0.
 static bool streams_small(const Plan* plan, int nq, const HostPass& hp) {
     if (plan->inst.size() != 1 || hp.sbits != hp.tbits || hp.nuref > 0) return false;
-    bool mat4 = false;
-    for (const HostStage& hs : hp.stages)
-        for (const Op& o : hs.ops) mat4 = mat4 || o.kind == OP_MAT4;
-    if (plan->prec == PK_FP64) return !mat4 && nq >= 17 && nq <= 20;
-    return mat4 && nq >= 20 && nq <= 22;
+    return plan->prec == PK_FP64 ? nq >= 17 && nq <= 20 : nq == 21 || nq == 22;
 }
 
 int recompile(Plan* plan, std::string* err) {

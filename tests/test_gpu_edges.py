@@ -357,3 +357,12 @@ def test_repeated_one_pass_list_combines_once():
     for _ in range(3):
         want, L, norm = pk.evaluate(plan, want)
     assert torch.equal(got[0], want) and torch.equal(got[1], L) and torch.equal(got[2], norm)
+
+
+@pytest.mark.parametrize("nq,prec,pairs,tile", [(17, "fp64", True, None), (20, "fp64", True, None), (20, "fp64", True, 8),
+                                                (20, "fp32", False, None), (21, "fp32", False, None),
+                                                (21, "fp32", True, None), (22, "fp32", False, 9), (23, "fp32", True, None)])
+def test_streamed_passes_whatever_the_gates(nq, prec, pairs, tile):
+    """States of a size that streams, with and without 4x4 gates in either precision (FP64
+    n_q = 17..20, FP32 21 and 22), and one size outside: as the test of small states above."""
+    test_streamed_passes_of_small_states(nq, prec, pairs, tile)

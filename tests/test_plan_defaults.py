@@ -220,3 +220,14 @@ def test_automatic_loop_is_not_mixed_while_the_caches_hold_the_state(kind, prec,
     gates = W.grover_gates((2, 2, 0.7, 0.4, 0.0)) if kind == "hadamards" else _mixed(kind, nq)
     plan = pk.Plan({"nq": nq, "gates": gates, "marked": [1]}, prec=prec)
     assert {p["overlap"] for p in _used(plan)["forward"]} == want
+
+
+@pytest.mark.parametrize("kind", ["one_cnot", "one_d4", "brickwork", "hadamards"])
+@pytest.mark.parametrize("prec,sizes", [("fp64", (17, 20)), ("fp32", (21, 22))])
+def test_small_states_stream_by_their_size(prec, sizes, kind):
+    """Whether the forward passes of a state about as large as the L2s stream follows from
+    its size, whatever 4x4 steps it holds."""
+    for nq in (sizes[0] - 1, *sizes, sizes[1] + 1):
+        gates = W.grover_gates((2, 2, 0.7, 0.4, 0.0)) if kind == "hadamards" else _mixed(kind, nq)
+        plan = pk.Plan({"nq": nq, "gates": gates, "marked": [1]}, prec=prec)
+        assert {p["stream"] for p in _used(plan)["forward"]} == {int(nq in sizes)}
