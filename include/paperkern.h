@@ -305,7 +305,7 @@ int pk_evaluate_static(pk_plan* plan, const void* psi_in, void* psi_out, double*
  * alone, first.  The whole sequence of passes, one launch each, is captured into
  * one hipGraph, keyed by the pointers and reps, and replayed.  With the environment
  * variable PK_REPEAT_PERSISTENT=1 (and reps > 1, every pass on one kernel
- * instance with 4 or 5 register bits) the passes run instead in one persistent launch of as many
+ * instance) the passes run instead in one persistent launch of as many
  * workgroups as the GPU holds at once, with a grid-wide barrier between passes;
  * same results bit for bit, but on MI355X the barrier's device-scope fences cost
  * more than the kernel boundaries.  If its workgroups cannot all be resident (the

@@ -19,7 +19,7 @@ LIB = os.path.join(HERE, "libpaperkern.so")
 # the pass and batched kernel instances come first: they take longest to compile
 SOURCES = [
     # longest compiles first, so that the parallel build ends with short ones
-    "pk_pass_f64r5.hip", "pk_batched_f64.hip", "pk_batched_f32.hip", "pk_pass_f64bwd.hip", "pk_pass_f32r5.hip",
+    "pk_pass_f64r5.hip", "pk_repeat_r3.hip", "pk_batched_f64.hip", "pk_batched_f32.hip", "pk_pass_f64bwd.hip", "pk_pass_f32r5.hip",
     "pk_pass_f32bwd.hip", "pk_pass_f64r3.hip", "pk_pass_f64t.hip", "pk_plan.cpp", "pk_api.cpp", "pk_search.hip",
     "pk_density.hip", "pk_shor.hip", "pk_kernels.hip", "pk_pass_f32r3.hip", "pk_repeat_f64.hip", "pk_pass_f64.hip",
     "pk_pass_f32.hip", "pk_repeat_f32.hip"]

@@ -424,7 +424,6 @@ bool repeat_persistent() {
 unsigned repeat_grid(DevPlan* d) {
     const Instance& in = d->host.inst[0];
     const int kmax = in.fwd[0].kmax, rbits = in.fwd[0].rbits;
-    if (rbits == 3) return 0;  // the persistent kernel has 4 and 5 register bits
     int64_t tiles = 0;
     for (const auto& hp : in.fwd) {
         if (hp.kmax != kmax || hp.rbits != rbits) return 0;

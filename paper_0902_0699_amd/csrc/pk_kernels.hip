@@ -202,12 +202,16 @@ hipError_t launch_repeat(const PassLaunch& L, const RepeatArgs& r, unsigned grid
     if (L.rbits == 5)
         return L.fp64 ? launch_repeat_r<double, 5>(L.kmax, a, r, grid, st)
                       : launch_repeat_r<float, 5>(L.kmax, a, r, grid, st);
+    if (L.rbits == 3)
+        return L.fp64 ? launch_repeat_r<double, 3>(L.kmax, a, r, grid, st)
+                      : launch_repeat_r<float, 3>(L.kmax, a, r, grid, st);
     return L.fp64 ? launch_repeat_r<double, 4>(L.kmax, a, r, grid, st)
                   : launch_repeat_r<float, 4>(L.kmax, a, r, grid, st);
 }
 
 int repeat_blocks_per_cu(int kmax, int rbits, bool fp64) {
     if (rbits == 5) return fp64 ? repeat_occupancy_r<double, 5>(kmax) : repeat_occupancy_r<float, 5>(kmax);
+    if (rbits == 3) return fp64 ? repeat_occupancy_r<double, 3>(kmax) : repeat_occupancy_r<float, 3>(kmax);
     return fp64 ? repeat_occupancy_r<double, 4>(kmax) : repeat_occupancy_r<float, 4>(kmax);
 }
 

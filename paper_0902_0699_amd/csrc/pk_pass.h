@@ -1394,18 +1394,22 @@ static int batched_occupancy_t() {
     return per_cu;
 }
 
-// Kernel instances of the batched launch: KMAX 10..13 (14 for FP32), RB 4 or 5.
+// Kernel instances of the batched launch (RB 4 or 5) and the persistent repeat launch
+// (also 3): KMAX RB + 6 .. 13, 14 for FP32 where a workgroup of 1024 threads holds it.
 template <typename R, int RB, typename F>
 static auto batched_instance(int kmax, F&& f) {
     switch (kmax) {
+    case 9:
+        if constexpr (RB == 3) return f(std::integral_constant<int, 9>{});
+        break;
     case 10:
-        if constexpr (RB == 4) return f(std::integral_constant<int, 10>{});
+        if constexpr (RB <= 4) return f(std::integral_constant<int, 10>{});
         break;
     case 11: return f(std::integral_constant<int, 11>{});
     case 12: return f(std::integral_constant<int, 12>{});
     case 13: return f(std::integral_constant<int, 13>{});
     case 14:
-        if constexpr (sizeof(R) == 4) return f(std::integral_constant<int, 14>{});
+        if constexpr (sizeof(R) == 4 && RB >= 4) return f(std::integral_constant<int, 14>{});
         break;
     default: break;
     }

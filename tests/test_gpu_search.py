@@ -271,3 +271,37 @@ def test_diffusion_variant_rejects_bad_arguments():
     for nq, marked, it in ((6, [64], 1), (6, [3, 3], 1), (6, [1], 0), (0, [0], 1)):
         with pytest.raises((pk.PaperkernError, ValueError)):
             pk.search_diffusion(nq, marked, it, x)
+
+
+@pytest.mark.parametrize("nq,prec,gates", [(8, "fp64", "grover"), (13, "fp64", "grover"), (18, "fp64", "grover"),
+                                           (18, "fp32", "grover"), (20, "fp32", "grover"), (20, "fp64", "qft")])
+def test_persistent_launch_with_the_automatic_setting(nq, prec, gates, monkeypatch):
+    """PK_REPEAT_PERSISTENT=1 is honoured where the library picks 3 register bits: with a
+    zero wait bound L and the norm are NaN (more than one workgroup, so a barrier gave up),
+    with the normal one the states equal the launch per pass bit for bit."""
+    pk = _pk()
+    reps = 7
+    glist = [("QFT", 1, nq)] if gates == "qft" else W.grover_gates((2, 3, 0.3, 0.4, 0.0))
+    dt = torch.complex128 if prec == "fp64" else torch.complex64
+    out = {}
+    for mode, spin in (("persistent", "0"), ("persistent", None), ("per_pass", None)):
+        monkeypatch.setenv("PK_REPEAT_PERSISTENT", "1" if mode == "persistent" else "0")
+        if spin is None:
+            monkeypatch.delenv("PK_BARRIER_SPIN_US", raising=False)
+        else:
+            monkeypatch.setenv("PK_BARRIER_SPIN_US", spin)
+        plan = pk.Plan({"nq": nq, "gates": glist, "marked": [3]}, prec=prec)
+        fwd = plan.describe()["instances"][0]["forward"]
+        assert {p["rbits"] for p in fwd} == {3}
+        _say("repeat n_q=%d %s %s: %s, bound %s" % (nq, prec, gates, mode, spin))
+        y, L, norm = pk.evaluate_repeat(plan, _uniform(nq, dt), reps)
+        torch.cuda.synchronize()
+        if spin is None:
+            out[mode] = (y, L.item(), norm.item())
+        elif nq > fwd[0]["k"]:
+            assert np.isnan(L.item()) and np.isnan(norm.item())
+    assert torch.equal(out["persistent"][0], out["per_pass"][0])
+    assert out["persistent"][1] == out["per_pass"][1]
+    # the norm's terms may be contracted differently by the two kernels: n + 2 roundings
+    u = 2.0 ** -53 if prec == "fp64" else 2.0 ** -24
+    assert abs(out["persistent"][2] - out["per_pass"][2]) <= 4 * u + (1 << nq) * 2.0 ** -53
