@@ -375,3 +375,63 @@ def test_full_size_backward_every_element():
     torch.cuda.empty_cache()
     assert nb == 7
     assert err <= TOL_GRAD
+
+
+@pytest.mark.parametrize("kind,nq,prec", [("grover", 17, "fp64"), ("grover", 24, "fp64"), ("phases", 20, "fp64"),
+                                          ("qft", 22, "fp64"), ("qft", 25, "fp64"), ("grover", 22, "fp32"),
+                                          ("phases", 18, "fp32"), ("qft", 24, "fp32")])
+@pytest.mark.parametrize("tile", [12, 13])
+def test_overlapped_and_plain_tile_loops_agree(kind, nq, prec, tile):
+    """The overlapped tile loop against the plain one, every pass, with 4 register bits and
+    tiles that fill the workgroup (asserted: elsewhere the setting changes nothing), with
+    and without product tables, under every walk: state and L bit for bit; the norm
+    partials, which the two loops may contract differently, as in the test above."""
+    pk = _pk()
+    rng = np.random.default_rng(800 + nq)
+    if kind == "grover":
+        gates, marked, psi = _case(nq, 2, 70 + nq)
+    else:
+        gates = W.phase_circuit(rng, nq, 40) if kind == "phases" else [("QFT", 1, nq)]
+        marked = [int(rng.integers(0, 1 << nq))]
+        v = rng.standard_normal(1 << nq) + 1j * rng.standard_normal(1 << nq)
+        psi = v / np.linalg.norm(v)
+    plan = pk.Plan({"nq": nq, "gates": gates, "marked": marked}, prec=prec)
+    plan.set_launch(0, 4)
+    plan.set_tiling(tile, 4)
+    inst = plan.describe()["instances"][0]
+    assert all(p["rbits"] == 4 and p["k"] == tile for p in inst["forward"])
+    x = torch.from_numpy(psi).to(torch.complex128 if prec == "fp64" else torch.complex64).to("cuda")
+    n = plan.passes()
+    ntol = 1e-12 if prec == "fp64" else 2.0 ** -23
+    for walks in ([0] * n, [2] * n, [-1] * n):
+        plan.set_pass_walk(walks)
+        res = []
+        for on in (0, 1):
+            plan.set_pass_overlap([on] * n)
+            assert all(p["overlap"] == on for p in plan.describe()["instances"][0]["used"]["forward"])
+            _say("loop %d, walk %d, tile %d: %s n_q=%d %s" % (on, walks[0], tile, kind, nq, prec))
+            res.append(pk.evaluate(plan, x))
+        (a, La, na), (b, Lb, nb) = res
+        assert torch.equal(a, b) and La.item() == Lb.item() and abs(na.item() - nb.item()) <= ntol * abs(na.item())
+
+
+@pytest.mark.parametrize("nq,prec", [(20, "fp64"), (24, "fp64"), (24, "fp32")])
+def test_tile_walks_against_the_strided_walk(nq, prec):
+    """Every walk against the strided one with the plain loop, both set by the caller: state
+    and L bit for bit; the norm, each of whose partials is summed by one of the loop's two
+    copies of the tile, to 1e-12 (FP32 2^-23) relative as above."""
+    pk = _pk()
+    gates, marked, psi = _case(nq, 3, 90 + nq)
+    plan = pk.Plan({"nq": nq, "gates": gates, "marked": marked}, prec=prec)
+    x = torch.from_numpy(psi).to(torch.complex128 if prec == "fp64" else torch.complex64).to("cuda")
+    n = plan.passes()
+    ntol = 1e-12 if prec == "fp64" else 2.0 ** -23
+    plan.set_pass_overlap([0] * n)
+    plan.set_pass_walk([0] * n)
+    a, La, na = pk.evaluate(plan, x)
+    for w in (2, 3, 64, -1):
+        plan.set_pass_walk([w] * n)
+        assert all(p["walk"] == w and p["overlap"] == 0 for p in plan.describe()["instances"][0]["used"]["forward"])
+        _say("walk %d n_q=%d %s" % (w, nq, prec))
+        b, Lb, nb = pk.evaluate(plan, x)
+        assert torch.equal(a, b) and La.item() == Lb.item() and abs(na.item() - nb.item()) <= ntol * abs(na.item())
