@@ -1492,9 +1492,8 @@ int compile_plan(Plan* plan, const pk_problem* probs, int n_inst, int prec, std:
 //    phases 25 .. 28 732 and 665, 1434 and 1367, 2730 and 2638, 5666 and 5143, T 30 39373
 //    and 38925; the line: G + 16 phases 25 .. 28 1208 and 1145, 2335 and 2367, 4452 and
 //    4562, 9376 and 9222, H + 6 phases 26 1229 and 1296).  A quarter as many phases, an
-//    eighth as many 4x4 steps as other gates are taken as dense.  A pass more
-//    costs all of it (T 25, 4 passes for 3, 1023 and 1069; QF + CNOT 30, 7 for 6, 62755
-//    and 65385).
+//    eighth as many 4x4 steps as other gates are taken as dense.  A pass more costs all of
+//    it (T 25, 4 passes for 3, 1023 and 1069; QF + CNOT 30, 7 for 6, 62755 and 65385).
 //  * FP32 tiles take half the LDS, so 2^12 pays longer: to 2^27 with any phase (G + one
 //    phase 23 149 and 141, 27 2261 and 2159) and with 4x4 steps even for a pass more (T
 //    25 710 and 626, 27 2846 and 2627), not at 2^28 (G + 8 CNOT, 6 for 5, 5458 and 6076).
@@ -1541,7 +1540,8 @@ static void choose_tiling(Plan* plan, CutCache* cuts) {
         if (fours || phases || (fp64 && (nq == 23 || nq == 24))) {
             const int rb12 = fp64 && nq <= 22 && !fours ? 3 : 4, more = passes(12, rb12) - passes(big, 4);
             if (nq <= 22)
-                small = more <= 0 && (fours ? mix.dense4() || (!fp64 && most_phases) : fp64 || nq == 21 || most_phases);
+                small = more <= 0 &&
+                        (fours ? mix.dense4() || (!fp64 && most_phases) : fp64 || nq == 21 || most_phases);
             else if (fp64)
                 small = more < 0 || (more == 0 && (nq <= 24 || mix.dense()));
             else if (nq <= 27)
@@ -1552,11 +1552,11 @@ static void choose_tiling(Plan* plan, CutCache* cuts) {
         t.tile_bits = small ? 12 : big;
         t.reg_bits = fp64 || small || nq == 21 || (nq == 22 && fours) || most_phases ? 4 : 5;
         // 2^12 FP64 tiles with phases take 8 amplitudes a thread to 2^22 (QF 22 207 with 16,
-        // 186), and from 2^27 where that takes at most a quarter more LDS exchanges: QF 10 of 27 .. 30
-        // (equal) 2351 and 2151, 4984 and 4334, 10566 and 9136, 19166 and 17560, QF 20 (5 for
-        // 4) 4282 and 4321, 8719 and 8669, 18470 and 17675, 35276 and 34428; QF 14 (3 for 2)
-        // 3080 and 3119, 6025 and 6266, QF 8 (2 for 1) 9380 and 11330.  Between, 16 are as
-        // fast or faster (QF 6 of 25 and 26, equal, 258 and 263, 478 and 500)
+        // 186), and from 2^27 where that takes at most a quarter more LDS exchanges: QF 10 of
+        // 27 .. 30 (equal) 2351 and 2151, 4984 and 4334, 10566 and 9136, 19166 and 17560, QF 20
+        // (5 for 4) 4282 and 4321, 8719 and 8669, 18470 and 17675, 35276 and 34428; QF 14 (3
+        // for 2) 3080 and 3119, 6025 and 6266, QF 8 of 30 (2 for 1) 9380 and 11330.  Between, 16
+        // are as fast or faster (QF 6 of 25 and 26, equal, 258 and 263, 478 and 500)
         if (fp64 && small && phases && !fours &&
             (nq <= 22 || (nq >= 27 && 4 * outline(plan, 12, 3, cuts, true).exchanges <=
                                           5 * outline(plan, 12, 4, cuts, true).exchanges)))
@@ -1577,11 +1577,11 @@ static void choose_tiling(Plan* plan, CutCache* cuts) {
 //    16 of 24 238 and 220), phases in FP64 from 2^11 tiles on (QF 14 of 22 FP64 112 and
 //    119, FP32 90 and 85).  Plain and overlapped passes mixed are slower than either while
 //    the state fits the caches (QF 15 of 23 225, H + 12 phases 23 165, 166 and 178), so only
-//    from 2^13 tiles on does a list with a few such steps overlap the passes that hold them (FP32 G + one phase 25 511 and
-//    491, FP64 1101 and 1089).
+//    from 2^13 tiles on does a list with a few such steps overlap the passes that hold
+//    them (FP32 G + one phase 25 511 and 491, FP64 1101 and 1089).
 static int32_t default_overlap(bool fp64, const GateMix& mix, const HostPass& hp) {
     if (hp.rbits != 4 || hp.ntiles < 1024 || hp.k < 12) return 0;
-    if (hp.flags & PASS_STREAM) return hp.ntiles < (1 << 16);
+    if ((hp.flags & PASS_STREAM) && hp.ntiles >= (1 << 16)) return 0;
     if (hp.k == 13) return 1;
     if (hp.k == 12 && (mix.dense4() || (mix.dense() && hp.ntiles >= (fp64 ? 2048 : 1024)))) return 1;
     bool heavy = !hp.phases.empty();
@@ -1728,7 +1728,8 @@ static int recompile_with(Plan* plan, std::string* err, CutCache* forward_cuts) 
             if (plan->inst.size() != 1) continue;
             if (streams_small(plan, plan->inst[i].nq, hp)) plan->passes.back().flags |= PASS_STREAM;
             plan->passes.back().walk = plan->walk.empty() ? 0 : plan->walk[p];
-            plan->passes.back().overlap = plan->overlap.empty() ? default_overlap(plan->prec == PK_FP64, mix, hp) : plan->overlap[p];
+            plan->passes.back().overlap =
+                plan->overlap.empty() ? default_overlap(plan->prec == PK_FP64, mix, hp) : plan->overlap[p];
         }
     plan->n_fwd_passes = (int)plan->passes.size();
     for (size_t i = 0; i < plan->inst.size(); ++i)

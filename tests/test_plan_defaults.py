@@ -213,12 +213,14 @@ def test_automatic_walk_is_strided(nq, prec):
     ("hadamards", "fp64", 22, {0}), ("hadamards", "fp64", 24, {0}), ("hadamards", "fp64", 26, {1}),
     ("qft_half", "fp64", 22, {0}), ("qft_half", "fp32", 22, {1}), ("qft_half", "fp64", 25, {1}), ("phases", "fp64", 23, {1}), ("phases", "fp32", 24, {1}),
     ("brickwork", "fp64", 22, {1}), ("one_phase", "fp64", 24, {0}), ("one_phase", "fp32", 23, {0}),
-    ("one_phase", "fp32", 25, {0, 1}), ("hadamards", "fp32", 26, {0})])
+    ("one_phase", "fp32", 25, {0, 1}), ("hadamards", "fp32", 26, {0}), ("small_tiles", "fp64", 26, {0})])
 def test_automatic_loop_is_not_mixed_while_the_caches_hold_the_state(kind, prec, nq, want):
     """Every pass overlaps or none does, but for a list with a few phases from 2^13 tiles
     on, whose passes with phases do."""
-    gates = W.grover_gates((2, 2, 0.7, 0.4, 0.0)) if kind == "hadamards" else _mixed(kind, nq)
+    gates = W.grover_gates((2, 2, 0.7, 0.4, 0.0)) if kind in ("hadamards", "small_tiles") else _mixed(kind, nq)
     plan = pk.Plan({"nq": nq, "gates": gates, "marked": [1]}, prec=prec)
+    if kind == "small_tiles":
+        plan.set_tiling(12, 4)
     assert {p["overlap"] for p in _used(plan)["forward"]} == want
 
 
