@@ -30,6 +30,7 @@ struct DevPlan {
     unsigned batch_grid = 0;  // persistent grid of the batched launch
     uint64_t spin_ticks = 0;  // half a second of the device wall clock
     DevPlan* fused = nullptr; // pk_evaluate_repeat: kRepeatFuse applications as one schedule
+    bool never_fused = false; // ... which these settings do not allow or gain nothing from
 };
 
 // pk_evaluate_repeat schedules this many consecutive applications of the gate list
@@ -74,6 +75,7 @@ void drop_graphs(DevPlan* d) {
     if (d->exec) hipGraphExecDestroy(reinterpret_cast<hipGraphExec_t>(d->exec));
     d->exec = nullptr;
     std::memset(d->key, 0, sizeof d->key);
+    d->never_fused = false;
     if (d->fused) {
         drop_device(d->fused);
         if (d->fused->cap) hipStreamDestroy(d->fused->cap);
@@ -322,11 +324,12 @@ hipError_t enqueue_eval(DevPlan* d, const EvalArgs& a, hipStream_t st, std::vect
 // settings, or nullptr where that does not apply: a plan with angle parameters
 // (each application would need its own), or one whose fused schedule would not use
 // the same workspace layout.  Built on first use and kept until the plan's
-// settings change.
+// settings change, as is the finding that it saves no pass: compiling it takes tens of
+// milliseconds for lists of 4x4 gates.
 DevPlan* fused_plan(DevPlan* d) {
     if (d->fused) return d->fused;
     const Plan& P = d->host;
-    if (P.inst.size() != 1 || !P.params.empty()) return nullptr;
+    if (d->never_fused || P.inst.size() != 1 || !P.params.empty()) return nullptr;
     DevPlan* f = new (std::nothrow) DevPlan();
     if (!f) return nullptr;
     f->host = P;
@@ -354,6 +357,7 @@ DevPlan* fused_plan(DevPlan* d) {
     }
     if (!same || f->host.inst[0].fwd.size() >= (size_t)kRepeatFuse * P.inst[0].fwd.size()) {
         delete f;
+        d->never_fused = true;
         return nullptr;
     }
     d->fused = f;

@@ -233,3 +233,23 @@ def test_small_states_stream_by_their_size(prec, sizes, kind):
         gates = W.grover_gates((2, 2, 0.7, 0.4, 0.0)) if kind == "hadamards" else _mixed(kind, nq)
         plan = pk.Plan({"nq": nq, "gates": gates, "marked": [1]}, prec=prec)
         assert {p["stream"] for p in _used(plan)["forward"]} == {int(nq in sizes)}
+
+
+def test_a_repeat_that_cannot_fuse_is_planned_once():
+    """A list whose eight applications take no fewer passes together than apart: the finding
+    is kept, so later calls do not compile the eight again (the first does), until a setting
+    changes the schedule."""
+    import time
+    plan = pk.Plan({"nq": 14, "gates": _mixed("brickwork", 14), "marked": [1]})
+
+    def timed(calls):
+        t = time.perf_counter()
+        n = [pk.repeat_launches(plan, 40) for _ in range(calls)]
+        return time.perf_counter() - t, set(n)
+
+    first, n = timed(1)
+    assert n == {40 * plan.passes()}  # nothing fused
+    later, n = timed(20)
+    assert n == {40 * plan.passes()} and later < first
+    plan.set_tiling(13, 4)
+    assert pk.repeat_launches(plan, 40) <= 40 * plan.passes()
