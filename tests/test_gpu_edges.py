@@ -366,3 +366,46 @@ def test_streamed_passes_whatever_the_gates(nq, prec, pairs, tile):
     """States of a size that streams, with and without 4x4 gates in either precision (FP64
     n_q = 17..20, FP32 21 and 22), and one size outside: as the test of small states above."""
     test_streamed_passes_of_small_states(nq, prec, pairs, tile)
+
+
+@pytest.mark.parametrize("nq,tile,angles", [(9, None, False), (13, None, True), (16, None, False), (15, 6, True)])
+def test_evaluations_in_a_caller_captured_graph(nq, tile, angles):
+    """pk_evaluate, pk_evaluate_static and pk_backward captured by the caller (tables uploaded
+    before): every replay, on new inputs, equals the eager calls bit for bit, with eager
+    evaluations of the same plan and workspace and synchronisations between the replays."""
+    pk = _pk()
+    plan = pk.Plan({"nq": nq, "gates": W.grover_gates((1, 3, 0.5, 0.8, 0.0)), "marked": [1, 6]})
+    if tile:
+        plan.set_tiling(tile, 3)
+    states = [torch.from_numpy(_state(nq, 20 + i)).to("cuda") for i in range(4)]
+    ang = torch.tensor([0.5, 0.8, 0.2], dtype=torch.float64, device="cuda") if angles else None
+    dL = torch.full((1,), 0.75, dtype=torch.float64, device="cuda")
+    x = states[0].clone()
+    y, z = torch.empty_like(x), torch.empty_like(x)
+    sums = torch.zeros(4, dtype=torch.float64, device="cuda")
+
+    def calls():
+        pk.evaluate_into(plan, x, y, sums[0:1], sums[1:2], angles=ang)
+        if not tile:
+            pk.evaluate_static(plan, x, z, sums[2:3], sums[3:4], angles=ang)
+        return pk.backward(plan, y, dL, angles=ang)
+
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        calls()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    print("captured n_q=%d tile %s angles %s" % (nq, tile, angles), flush=True)
+    with torch.cuda.graph(graph):
+        gpsi, gang = calls()
+    for i, s in enumerate(states):
+        want, L, norm = pk.evaluate(plan, s, angles=ang)
+        wpsi, wang = pk.backward(plan, want, dL, angles=ang)
+        torch.cuda.synchronize()
+        x.copy_(s)
+        sums.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, want) and torch.equal(gpsi, wpsi) and torch.equal(gang, wang), i
+        assert torch.equal(sums[:2], torch.cat([L, norm]))
+        assert tile or (torch.equal(z, want) and torch.equal(sums[2:], sums[:2]))
