@@ -266,9 +266,9 @@ int pk_workspace_bytes(const pk_plan* plan, int32_t op, int64_t* bytes);
  *   angles   device double[3 * n_rot] or NULL (n_rot = D2 and D4 gates; NULL = the
  *            angles given to pk_create)
  *   workspace device, >= pk_workspace_bytes(PK_OP_EVAL)
- * The launches (one per pass, one before them where `angles` are given, one after them
- * where the last pass is the only one or has more than 4096 tiles) go to `stream`
- * directly.  Errors: PK_EINVAL (NULL/misaligned pointer, batched plan), PK_EDEVICE.
+ * The launches go to `stream` directly: one per pass, one before them where `angles` are
+ * given, one after them for the readouts of a last pass of more than 4096 tiles, or of a
+ * single pass of more than one.  Errors: PK_EINVAL (NULL/misaligned pointer, batched plan), PK_EDEVICE.
  */
 int pk_evaluate(pk_plan* plan, const void* psi_in, void* psi_out, double* L_out, double* norm_out,
                 const double* angles, void* workspace, void* stream);
